@@ -14,7 +14,7 @@ A case is a dict of plain values.  ``kind`` names the path:
 
 ``model`` names the lattice: ``square`` (one site with ``norb`` orbitals), ``two_site`` (a site with ``norb`` orbitals and
 one with a single orbital), ``graphene`` (two one-orbital sites, Ohno interaction) or ``cubic`` (one site, n x n x n mesh).
-Models and DLR node positions are input data; they come from the package's generators 
+Models and DLR node positions are input data; they come from the package's generators.
 The values in 64 bits that ``exact`` returns are computed here with torch alone.
 """
 import functools
