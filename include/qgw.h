@@ -499,7 +499,8 @@ typedef struct qgw_state_s *qgw_state;
 
 /* A self-consistent GW state bound to a plan: holds H0(k), V(q) and every
  * intermediate array on the device.  H0_R: [n_o][n_o][N_k] and V_R:
- * [N_b][N_b][N_k] are device arrays in R (FP64).  mixing in (0, 1] is the
+ * [N_b][N_b][N_k] are device arrays in R (FP64); the call reads V(R) once for
+ * its pair-exchange symmetry and waits for that.  mixing in (0, 1] is the
  * linear mixing weight of the total self-energy (1 = none).  The state owns
  * a second stream (default priority) on which each qgw_gw_iteration runs its
  * a12 beside a1-a11; it is forked from and joined back into the caller's
@@ -557,8 +558,13 @@ qgw_status qgw_state_hf_solve(qgw_state state, double tol, int32_t max_iter,
  * ``stream``: which = 0 G(k, i w) [orbital], 1 Sigma^C(k, i w) [orbital],
  * 2 Sigma_HF(k) [static orbital], 3 P(q, i nu) [pair matrix],
  * 4 W^C(q, i nu) [pair matrix], 5 n(k) [static orbital; the density of the
- * last Hartree-Fock pass or of the last GW iteration's a12].  *bytes (if not
- * NULL) receives the size. */
+ * last Hartree-Fock pass or of the last GW iteration's a12].  3 and 4 are
+ * those of the last FP64 iteration.  A state whose V(R) is unchanged under
+ * i <-> l of both pair indices holds them summed and stored per unordered
+ * pair: 4 is then spread over the members of each pair, and 3 is formed in
+ * the full basis from that iteration's G(tau), one bubble and one map queued
+ * on ``stream`` through the state's scratch.  *bytes (if not NULL) receives
+ * the size. */
 qgw_status qgw_state_copy(qgw_state state, int32_t which, void *dst, int64_t *bytes,
                           void *stream);
 

@@ -33,6 +33,12 @@ struct qgw_state_s {
   void *G_iw = nullptr, *Sig_iw = nullptr, *Sig_iw_old = nullptr, *SigHF_k = nullptr, *SigHF_old = nullptr;
   void *n_k = nullptr, *n_R = nullptr, *SigHF_R = nullptr, *Hs_k = nullptr;
   void *G_tau = nullptr, *G_reflt = nullptr, *Sig_tau_k = nullptr;
+  // V(R) has the pair-exchange symmetry: the pair arrays are kept in the folded basis of the plan copy pf.
+  // G_tau_R, G_reflt_R (folded states) hold the last FP64 iteration's G(R, tau) and G(R, beta - tau), from which
+  // qgw_state_copy forms that iteration's P in the full basis
+  bool folded = false;
+  Plan pf;
+  void *G_tau_R = nullptr, *G_reflt_R = nullptr;
   // pair
   void *Pq = nullptr, *P_nu = nullptr, *Wc_nu = nullptr;
   void* hf_ws = nullptr;  // Hartree-Fock solve: eigenvectors and eigenvalues per k
@@ -134,6 +140,16 @@ static bool nb_supported(int nb) {
       return false;
   }
 }
+static bool folded_nb_supported(int nb) {
+  switch (nb) {
+#define QGW_CASE(NN) case NN:
+    QGW_FOR_EACH_NB_FOLDED(QGW_CASE)
+#undef QGW_CASE
+    return true;
+    default:
+      return nb_supported(nb);
+  }
+}
 
 static size_t csize(const Plan& p) { return p.prec == 0 ? 16 : 8; }
 
@@ -144,7 +160,8 @@ static void free_plan_device(Plan& p) {
     p.dmaps64.m[m] = p.dmaps32.m[m] = nullptr;
   }
   void* ptrs[] = {p.d_tw64, p.d_tw32, p.d_pairs, p.terms.d_terms, p.terms.d_off, p.terms_lj.d_terms,
-                  p.terms_lj.d_off, p.d_wn, p.d_qp_row, p.d_partials, p.d_status, p.d_scalars, p.d_mf};
+                  p.terms_lj.d_off, p.d_wn, p.d_qp_row, p.d_partials, p.d_status, p.d_scalars, p.d_mf,
+                  p.d_fold_pairs, p.fold_terms.d_terms};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   p.d_tw64 = nullptr;
@@ -158,6 +175,7 @@ static void free_plan_device(Plan& p) {
   p.d_status = nullptr;
   p.d_scalars = nullptr;
   p.d_mf = nullptr;
+  p.d_fold_pairs = p.fold_terms.d_terms = p.fold_terms.d_off = nullptr;
 }
 
 // e^{i pi q / den} with q reduced exactly modulo 2 den first
@@ -389,6 +407,24 @@ static qgw_status plan_create_impl(const qgw_plan_desc* d, int mf_nodes, qgw_pla
       if (cnt > max_lj) max_lj = cnt;
     }
   p.terms_lj.max_terms = max_lj;
+  // the folded pair basis: classes of (i, l) and (l, i), numbered site by site, i then l >= i
+  std::vector<int> cls(nb, -1), ffirst, fsecond;
+  for (int a = 0; a < nb; ++a) {
+    if (p.pair_first[a] > p.pair_second[a]) continue;
+    cls[a] = int(ffirst.size());
+    cls[p.pair_of[size_t(p.pair_second[a]) * no + p.pair_first[a]]] = cls[a];
+    ffirst.push_back(p.pair_first[a]);
+    fsecond.push_back(p.pair_second[a]);
+  }
+  const int nf = int(ffirst.size());
+  if (nf < nb && folded_nb_supported(nf)) p.fold_nb = nf;
+  std::vector<int> fold_pairs(ffirst), fold_terms(terms);
+  fold_pairs.insert(fold_pairs.end(), fsecond.begin(), fsecond.end());
+  fold_pairs.insert(fold_pairs.end(), cls.begin(), cls.end());
+  for (size_t i = 0; i < fold_terms.size(); i += 4) {
+    fold_terms[i] = cls[fold_terms[i]];
+    fold_terms[i + 1] = cls[fold_terms[i + 1]];
+  }
   // DLR maps (FP64, host)
   std::string err;
   if (p.grid == kGridMF) {
@@ -466,6 +502,12 @@ static qgw_status plan_create_impl(const qgw_plan_desc* d, int mf_nodes, qgw_pla
   }
   if (e == hipSuccess) e = upload((void**)&p.terms.d_terms, terms.data(), terms.size() * sizeof(int));
   if (e == hipSuccess) e = upload((void**)&p.terms.d_off, toff.data(), toff.size() * sizeof(int));
+  if (e == hipSuccess && p.fold_nb)
+    e = upload((void**)&p.d_fold_pairs, fold_pairs.data(), fold_pairs.size() * sizeof(int));
+  if (e == hipSuccess && p.fold_nb)
+    e = upload((void**)&p.fold_terms.d_terms, fold_terms.data(), fold_terms.size() * sizeof(int));
+  p.fold_terms.d_off = p.terms.d_off;  // the same outputs and term counts (owned by terms)
+  p.fold_terms.max_terms = p.terms.max_terms;
   if (e == hipSuccess) e = upload((void**)&p.terms_lj.d_terms, terms_lj.data(), terms_lj.size() * sizeof(int));
   if (e == hipSuccess) e = upload((void**)&p.terms_lj.d_off, toff_lj.data(), toff_lj.size() * sizeof(int));
   if (e == hipSuccess) {
@@ -1276,7 +1318,7 @@ static void free_state(qgw_state st) {
                   st->SigHF_k, st->SigHF_old, st->n_k, st->n_R, st->SigHF_R, st->Hs_k, st->G_tau,
                   st->G_reflt, st->Sig_tau_k, st->Pq, st->P_nu, st->Wc_nu, st->d_dsig, st->d_blockmax,
                   st->G32, st->Gt32, st->Gr32, st->St32, st->Siw32, st->Pq32, st->Pnu32, st->Wc32,
-                  st->Vqm32, st->d_scal, st->d_part, st->d_stat, st->hf_ws};
+                  st->Vqm32, st->d_scal, st->d_part, st->d_stat, st->hf_ws, st->G_tau_R, st->G_reflt_R};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
 }
@@ -1284,7 +1326,7 @@ static void free_state(qgw_state st) {
 // buffers of the single-precision phase, allocated when first needed
 static hipError_t ensure_fp32(qgw_state st) {
   if (st->has32) return hipSuccess;
-  const Plan& p = st->plan->p;
+  const Plan& p = st->folded ? st->pf : st->plan->p;
   const size_t so = size_t(p.no) * p.no * p.nk * 8;
   const size_t sp = size_t(p.nb) * p.nb * p.nk * 8;
   const size_t fo = so * p.r, fp = sp * p.r;
@@ -1324,8 +1366,22 @@ qgw_status qgw_state_create(qgw_plan h, const void* H0_R, const void* V_R, doubl
   const size_t sp = size_t(p.nb) * p.nb * p.nk * 16;         // static pair
   const size_t fo = so * p.r;                                // fermionic orbital
   const size_t fp = sp * p.r;                                // pair with nodes
-  const size_t fw = size_t(state_w_ld(p)) * p.nk * 16 * p.r;  // W^C: matrix rows padded to whole lines
   hipError_t e = hipSuccess;
+  // whether V(R) is unchanged under i <-> l of its pair indices (it is for real orbitals): a read of V, once per state
+  if (p.fold_nb) {
+    int flag = 1;
+    int* d_flag = nullptr;
+    e = hipMalloc((void**)&d_flag, sizeof(int));
+    if (e == hipSuccess) e = hipMemsetAsync(d_flag, 0, sizeof(int), nullptr);
+    if (e == hipSuccess) e = launch_fold_check(p, V_R, d_flag, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(&flag, d_flag, sizeof(int), hipMemcpyDeviceToHost);
+    if (d_flag) (void)hipFree(d_flag);
+    st->folded = e == hipSuccess && flag == 0;
+    if (st->folded) st->pf = fold_plan(p);
+  }
+  const Plan& pw = st->folded ? st->pf : p;
+  const size_t fpn = size_t(pw.nb) * pw.nb * p.nk * 16 * p.r;  // pair with nodes, in the state's basis
+  const size_t fw = size_t(state_w_ld(pw)) * p.nk * 16 * p.r;  // W^C: matrix rows padded to whole lines
   struct {
     void** ptr;
     size_t bytes;
@@ -1333,7 +1389,7 @@ qgw_status qgw_state_create(qgw_plan h, const void* H0_R, const void* V_R, doubl
                 {&st->V_q0, size_t(p.nb) * p.nb * 16},    {&st->G_iw, fo},       {&st->Sig_iw, fo},
                 {&st->Sig_iw_old, fo}, {&st->SigHF_k, so}, {&st->SigHF_old, so},  {&st->n_k, so},
                 {&st->n_R, so},       {&st->SigHF_R, so}, {&st->Hs_k, so},       {&st->G_tau, fo},
-                {&st->G_reflt, fo},   {&st->Sig_tau_k, fo}, {&st->Pq, fp},       {&st->P_nu, fp},
+                {&st->G_reflt, fo},   {&st->Sig_tau_k, fo}, {&st->Pq, fp},       {&st->P_nu, fpn},
                 {&st->Wc_nu, fw},     {(void**)&st->d_dsig, 64}, {(void**)&st->d_blockmax, 8192 * sizeof(double)},
                 {(void**)&st->d_scal, 32 * sizeof(double)},
                 {(void**)&st->d_part, size_t(8) * p.max_blocks * sizeof(double)},
@@ -1343,18 +1399,28 @@ qgw_status qgw_state_create(qgw_plan h, const void* H0_R, const void* V_R, doubl
     if (e != hipSuccess) break;
     e = hipMalloc(a.ptr, a.bytes);
   }
+  if (st->folded) {
+    if (e == hipSuccess) e = hipMalloc(&st->G_tau_R, fo);
+    if (e == hipSuccess) e = hipMalloc(&st->G_reflt_R, fo);
+    if (e == hipSuccess) e = hipMemsetAsync(st->G_tau_R, 0, fo, nullptr);
+    if (e == hipSuccess) e = hipMemsetAsync(st->G_reflt_R, 0, fo, nullptr);
+  }
   if (e == hipSuccess) e = hipHostMalloc((void**)&st->h_io, 32 * sizeof(double), hipHostMallocDefault);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&st->ev_io, hipEventDisableTiming);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&st->side, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&st->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&st->ev_join, hipEventDisableTiming);
-  st->p32 = p;
+  st->p32 = pw;
   st->p32.prec = QGW_F32;
   hipStream_t s = nullptr;
   if (e == hipSuccess) e = hipMemcpyAsync(st->V_R, V_R, sp, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess) e = launch_lattice_fft(p, QGW_R_TO_K, int64_t(p.no) * p.no, H0_R, st->H_k, s);
   if (e == hipSuccess) e = launch_lattice_fft(p, QGW_R_TO_K, int64_t(p.nb) * p.nb, V_R, st->V_q, s);
   if (e == hipSuccess) e = launch_slab_to_matrix_static(p, st->V_q, st->V_qm, s);
+  if (e == hipSuccess && st->folded) {
+    e = launch_fold_matrix(p, p.nk, st->V_qm, st->V_q, s);  // the slab form is not read again
+    std::swap(st->V_q, st->V_qm);
+  }
   if (e == hipSuccess) e = launch_pair_sum_r(p, V_R, st->V_q0, s);
   if (e == hipSuccess) {
     double sc[16];
@@ -1479,6 +1545,10 @@ static hipError_t enqueue_steps(qgw_state st, bool f32, bool prof, hipStream_t s
   const int64_t no2 = int64_t(p.no) * p.no;
   const int64_t ncol_g = no2 * p.nk;
   st->p32.tune = p.has_tune32 ? p.tune32 : p.tune;
+  st->pf.tune = p.tune;
+  const Plan& pw = st->folded ? st->pf : p;  // the pair arrays' basis
+  void* const gt = st->folded ? st->G_tau_R : st->G_tau;
+  void* const gr = st->folded ? st->G_reflt_R : st->G_reflt;
   hipError_t e = hipSuccess;
   hipEvent_t* ev = st->ev[st->ev_set];
   const uint32_t m = prof ? st->prof_mask : 0u;
@@ -1507,17 +1577,18 @@ static hipError_t enqueue_steps(qgw_state st, bool f32, bool prof, hipStream_t s
   if (!a1_queued) run(enqueue_a1(st, f32, prof, s, fork, st->ev_set));
   if (!f32) {
     mark(2);  // a2
-    run(launch_lattice_fft2(p, QGW_K_TO_R, no2 * p.r, st->G_tau, st->G_tau, st->G_reflt, st->G_reflt, s));
+    run(launch_lattice_fft2(p, QGW_K_TO_R, no2 * p.r, st->G_tau, gt, st->G_reflt, gr, s));
     mark(3);  // a3 + a4
-    run(launch_bubble(p, st->G_tau, st->G_reflt, 1, st->Pq, s));
+    run(launch_bubble(pw, gt, gr, 1, st->Pq, s));
     mark(4);  // a5
-    run(launch_dlr_pairs(p, QGW_B_TAU2IW, QGW_LAYOUT_SLAB, QGW_LAYOUT_MATRIX, st->Pq, st->P_nu, s));
+    run(launch_dlr_pairs(pw, QGW_B_TAU2IW, QGW_LAYOUT_SLAB, QGW_LAYOUT_MATRIX, st->Pq, st->P_nu, s));
     mark(5);  // a6
-    run(launch_dyson_w(p, st->V_qm, st->P_nu, st->Wc_nu, s, state_w_ld(p)));
+    run(launch_dyson_w(pw, st->V_qm, st->P_nu, st->Wc_nu, s, state_w_ld(pw)));
     mark(6);  // a7
-    run(launch_dlr_pairs(p, QGW_B_IW2TAU, QGW_LAYOUT_MATRIX, QGW_LAYOUT_SLAB, st->Wc_nu, st->Pq, s, state_w_ld(p)));
+    run(launch_dlr_pairs(pw, QGW_B_IW2TAU, QGW_LAYOUT_MATRIX, QGW_LAYOUT_SLAB, st->Wc_nu, st->Pq, s,
+                         state_w_ld(pw)));
     mark(7);  // a8 + a9 + a10
-    run(launch_sigma(p, st->G_tau, st->Pq, 1, 1, st->Sig_tau_k, s));
+    run(launch_sigma(pw, gt, st->Pq, 1, 1, st->Sig_tau_k, s));
     mark(8);  // a11 (Hermitian part of Sigma^C(k, tau))
     run(launch_dlr(p, QGW_F_TAU2IW, ncol_g, 1.0, 0.0, st->Sig_tau_k, st->Sig_iw, s, 1));
   } else {
@@ -1530,9 +1601,9 @@ static hipError_t enqueue_steps(qgw_state st, bool f32, bool prof, hipStream_t s
     mark(4);
     run(launch_dlr_pairs(q, QGW_B_TAU2IW, QGW_LAYOUT_SLAB, QGW_LAYOUT_MATRIX, st->Pq32, st->Pnu32, s));
     mark(5);
-    run(launch_dyson_w(q, st->Vqm32, st->Pnu32, st->Wc32, s, state_w_ld(p)));
+    run(launch_dyson_w(q, st->Vqm32, st->Pnu32, st->Wc32, s, state_w_ld(q)));
     mark(6);
-    run(launch_dlr_pairs(q, QGW_B_IW2TAU, QGW_LAYOUT_MATRIX, QGW_LAYOUT_SLAB, st->Wc32, st->Pq32, s, state_w_ld(p)));
+    run(launch_dlr_pairs(q, QGW_B_IW2TAU, QGW_LAYOUT_MATRIX, QGW_LAYOUT_SLAB, st->Wc32, st->Pq32, s, state_w_ld(q)));
     mark(7);
     run(launch_sigma(q, st->Gt32, st->Pq32, 1, 1, st->St32, s));
     mark(8);
@@ -1756,7 +1827,7 @@ qgw_status qgw_batch_create(int32_t n, const qgw_state* states, int32_t precisio
     std::vector<int> order(n);
     for (int i = 0; i < n; ++i) order[i] = i;
     std::vector<double> cost(n);
-    for (int i = 0; i < n; ++i) cost[i] = iteration_cost_ns(states[i]->plan->p);
+    for (int i = 0; i < n; ++i) cost[i] = iteration_cost_ns(states[i]->folded ? states[i]->pf : states[i]->plan->p);
     std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return cost[a] > cost[c]; });
     std::vector<double> load(nw, 0.0);
     for (int i : order) {
@@ -1866,6 +1937,19 @@ qgw_status qgw_state_copy(qgw_state st, int32_t which, void* dst, int64_t* bytes
   if (bytes) *bytes = int64_t(n);
   if (!dst) return QGW_OK;
   QGW_CHECK_HIP(enter_device(p.device), "hipSetDevice");
+  if (st->folded && which == 3) {
+    // the bubble in the full basis from the G(tau) of the last FP64 iteration, through the state's slab buffer
+    hipStream_t s = (hipStream_t)stream;
+    QGW_CHECK_HIP(launch_bubble(p, st->G_tau_R, st->G_reflt_R, 1, st->Pq, s), "qgw_state_copy");
+    QGW_CHECK_HIP(launch_dlr_pairs(p, QGW_B_TAU2IW, QGW_LAYOUT_SLAB, QGW_LAYOUT_MATRIX, st->Pq, dst, s),
+                  "qgw_state_copy");
+    return QGW_OK;
+  }
+  if (st->folded && which == 4) {
+    QGW_CHECK_HIP(launch_unfold_matrix(p, int64_t(p.r) * p.nk, st->Wc_nu, state_w_ld(st->pf), dst,
+                                       (hipStream_t)stream), "qgw_state_copy");
+    return QGW_OK;
+  }
   const int64_t nb2 = int64_t(p.nb) * p.nb, ld = state_w_ld(p);
   if (which == 4 && ld != nb2)
     QGW_CHECK_HIP(hipMemcpy2DAsync(dst, size_t(nb2) * 16, src, size_t(ld) * 16, size_t(nb2) * 16,

@@ -1461,6 +1461,7 @@ hipError_t launch_dyson_w(const Plan& p, const void* v_q, const void* p_nu, void
     return p.prec == 0 ? dyson_w_nb<NBV, double>(p, v_q, p_nu, wc_nu, s, out_ld)          \
                        : dyson_w_nb<NBV, float>(p, v_q, p_nu, wc_nu, s, out_ld);
     QGW_FOR_EACH_NB(QGW_CASE)
+    QGW_FOR_EACH_NB_FOLDED(QGW_CASE)
 #undef QGW_CASE
     default:
       return hipErrorInvalidValue;

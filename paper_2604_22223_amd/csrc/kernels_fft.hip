@@ -66,8 +66,11 @@ __global__ __launch_bounds__(256) void k_lattice_fft(const cpx<T>* __restrict__ 
 // ---------------------------------------------------------------------------
 // bubble: P_{(il),(jk)}(R, tau) = -2 G_{lj}(R, tau) G_{ki}(-R, beta - tau)
 // slab index = (t * nb + alpha) * nb + beta
+// FOLD: alpha and beta are classes of the folded pair basis, and the products are summed over the members (i l), (l i)
+// and (j k), (k j) of both before the transform: as many products per node as without it (they read G from L2), but
+// N_b (N_b in classes) squared transforms and stores, 225 instead of 625 for five orbitals.
 // ---------------------------------------------------------------------------
-template <int N, bool OUTQ, typename T>
+template <int N, bool OUTQ, typename T, bool FOLD = false>
 __global__ __launch_bounds__(256) void k_bubble(const cpx<T>* __restrict__ gt,
                                                 const cpx<T>* __restrict__ gr,
                                                 cpx<T>* __restrict__ out, int64_t nslabs, int spb,
@@ -104,13 +107,29 @@ __global__ __launch_bounds__(256) void k_bubble(const cpx<T>* __restrict__ gt,
     const int be = int(s % nb), al = int((s / nb) % nb);
     const int64_t t = s / (int64_t(nb) * nb);
     const int i = pairs[al], l = pairs[nb + al], j = pairs[be], k = pairs[nb + be];
-    const cpx<T>* a = gt + ((t * no + l) * no + j) * M::NN;
-    const cpx<T>* b = gr + ((t * no + k) * no + i) * M::NN;
     const int mr2 = (N - line) % N;
+    if constexpr (FOLD) {
 #pragma unroll
-    for (int r1 = 0; r1 < N; ++r1) {
-      const int mr1 = (N - r1) % N;
-      x[r1] = scale(a[r1 * N + line] * b[mr1 * N + mr2], -two);
+      for (int r1 = 0; r1 < N; ++r1) x[r1] = mk(T(0), T(0));
+      const int ca = i == l ? 1 : 2, cb = j == k ? 1 : 2;
+      for (int c = 0; c < ca * cb; ++c) {
+        const bool sa = c >= cb, sb = (c & (cb - 1)) != 0;  // exchange the pair's members
+        const int ci = sa ? l : i, cl = sa ? i : l, cj = sb ? k : j, ck = sb ? j : k;
+        const cpx<T>* a = gt + ((t * no + cl) * no + cj) * M::NN;
+        const cpx<T>* b = gr + ((t * no + ck) * no + ci) * M::NN;
+#pragma unroll
+        for (int r1 = 0; r1 < N; ++r1) x[r1] = fma(x[r1], a[r1 * N + line], b[((N - r1) % N) * N + mr2]);
+      }
+#pragma unroll
+      for (int r1 = 0; r1 < N; ++r1) x[r1] = scale(x[r1], -two);
+    } else {
+      const cpx<T>* a = gt + ((t * no + l) * no + j) * M::NN;
+      const cpx<T>* b = gr + ((t * no + k) * no + i) * M::NN;
+#pragma unroll
+      for (int r1 = 0; r1 < N; ++r1) {
+        const int mr1 = (N - r1) % N;
+        x[r1] = scale(a[r1 * N + line] * b[mr1 * N + mr2], -two);
+      }
     }
     fft_reg<N, -1>(x, tw);  // along R1 -> q1
     cpx<T>* slab = lds + sl * M::SLAB;
@@ -303,7 +322,13 @@ hipError_t bubble_n(const Plan& p, const void* gt, const void* gr, int out_q, vo
   const int want = p.tune.bubble_spb > 0 ? p.tune.bubble_spb : (sizeof(T) == 8 && N >= 16 ? 2 : 0);
   const int spb = tuned_spb<T>(N, want);
   const int64_t blocks = (nslabs + spb - 1) / spb;
-  if (out_q) {
+  if (p.folded) {
+    if (!out_q) return hipErrorInvalidValue;
+    const size_t lds = size_t(spb) * MeshShape<N>::SLAB * sizeof(cpx<T>);
+    hipLaunchKernelGGL((k_bubble<N, true, T, true>), dim3(unsigned(blocks)), dim3(spb * N), lds, s,
+                       (const cpx<T>*)gt, (const cpx<T>*)gr, (cpx<T>*)out, nslabs, spb, p.no, p.nb,
+                       p.d_pairs, twiddles<T>(p));
+  } else if (out_q) {
     const size_t lds = size_t(spb) * MeshShape<N>::SLAB * sizeof(cpx<T>);
     hipLaunchKernelGGL((k_bubble<N, true, T>), dim3(unsigned(blocks)), dim3(spb * N), lds, s,
                        (const cpx<T>*)gt, (const cpx<T>*)gr, (cpx<T>*)out, nslabs, spb, p.no, p.nb,

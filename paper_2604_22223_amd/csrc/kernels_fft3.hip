@@ -134,7 +134,8 @@ __global__ __launch_bounds__(256) void k_lattice_fft3(const cpx<T>* __restrict__
 // ---------------------------------------------------------------------------
 // bubble: P_{(il),(jk)}(R, tau) = -2 G_{lj}(R, tau) G_{ki}(-R, beta - tau), slab (t, alpha, beta)
 // ---------------------------------------------------------------------------
-template <int N, bool OUTQ, typename T>
+// FOLD: summed over the members of the classes alpha and beta of the folded pair basis, as in the 2-D form
+template <int N, bool OUTQ, typename T, bool FOLD = false>
 __global__ __launch_bounds__(256) void k_bubble3(const cpx<T>* __restrict__ gt, const cpx<T>* __restrict__ gr,
                                                  cpx<T>* __restrict__ out, int64_t nslabs, int spb, int no, int nb,
                                                  const int* __restrict__ pairs, const cpx<T>* __restrict__ tw) {
@@ -166,11 +167,27 @@ __global__ __launch_bounds__(256) void k_bubble3(const cpx<T>* __restrict__ gt, 
     const int be = int(s % nb), al = int((s / nb) % nb);
     const int64_t t = s / (int64_t(nb) * nb);
     const int i = pairs[al], li = pairs[nb + al], j = pairs[be], k = pairs[nb + be];
-    const cpx<T>* a = gt + ((t * no + li) * no + j) * C::NK;
-    const cpx<T>* b = gr + ((t * no + k) * no + i) * C::NK;
     cpx<T> x[N];
+    if constexpr (FOLD) {
 #pragma unroll
-    for (int r1 = 0; r1 < N; ++r1) x[r1] = scale(a[r1 * C::LINES + l] * b[C::neg_axis1(r1, l)], -two);
+      for (int r1 = 0; r1 < N; ++r1) x[r1] = mk(T(0), T(0));
+      const int ca = i == li ? 1 : 2, cb = j == k ? 1 : 2;
+      for (int c = 0; c < ca * cb; ++c) {
+        const bool sa = c >= cb, sb = (c & (cb - 1)) != 0;  // exchange the pair's members
+        const int ci = sa ? li : i, cl = sa ? i : li, cj = sb ? k : j, ck = sb ? j : k;
+        const cpx<T>* a = gt + ((t * no + cl) * no + cj) * C::NK;
+        const cpx<T>* b = gr + ((t * no + ck) * no + ci) * C::NK;
+#pragma unroll
+        for (int r1 = 0; r1 < N; ++r1) x[r1] = fma(x[r1], a[r1 * C::LINES + l], b[C::neg_axis1(r1, l)]);
+      }
+#pragma unroll
+      for (int r1 = 0; r1 < N; ++r1) x[r1] = scale(x[r1], -two);
+    } else {
+      const cpx<T>* a = gt + ((t * no + li) * no + j) * C::NK;
+      const cpx<T>* b = gr + ((t * no + k) * no + i) * C::NK;
+#pragma unroll
+      for (int r1 = 0; r1 < N; ++r1) x[r1] = scale(a[r1 * C::LINES + l] * b[C::neg_axis1(r1, l)], -two);
+    }
     fft_reg<N, -1>(x, tw);  // R1 -> q1
     store_axis1<N>(slab, l, x);
   }
@@ -444,7 +461,12 @@ hipError_t bubble3_n(const Plan& p, const void* gt, const void* gr, int out_q, v
   const int spb = cube_spb<N, T>(p.tune.bubble_spb);
   const int64_t blocks = (nslabs + spb - 1) / spb;
   const dim3 blk(spb * Cube<N>::LINES);
-  if (out_q)
+  if (p.folded) {
+    if (!out_q) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_bubble3<N, true, T, true>), dim3(unsigned(blocks)), blk,
+                       size_t(spb) * Cube<N>::SLAB * sizeof(cpx<T>), s, (const cpx<T>*)gt, (const cpx<T>*)gr,
+                       (cpx<T>*)out, nslabs, spb, p.no, p.nb, p.d_pairs, tw3<T>(p));
+  } else if (out_q)
     hipLaunchKernelGGL((k_bubble3<N, true, T>), dim3(unsigned(blocks)), blk,
                        size_t(spb) * Cube<N>::SLAB * sizeof(cpx<T>), s, (const cpx<T>*)gt, (const cpx<T>*)gr,
                        (cpx<T>*)out, nslabs, spb, p.no, p.nb, p.d_pairs, tw3<T>(p));

@@ -80,6 +80,44 @@ __global__ void k_static_transpose(const zd* __restrict__ in, zd* __restrict__ o
   out[gi] = in[int64_t(a) * nq + q];
 }
 
+// flag |= 1 where V(R) [N_b][N_b][N_k] differs between a pair and its exchanged partner, in either index
+__global__ __launch_bounds__(256) void k_fold_check(const zd* __restrict__ v, int nb, int nk, int no,
+                                                    const int* __restrict__ pairs, int* __restrict__ flag) {
+  const int al = blockIdx.x / nb, be = blockIdx.x - al * nb;
+  const int* of = pairs + 2 * nb;  // pair index of (a, b)
+  const int sa = of[pairs[nb + al] * no + pairs[al]], sb = of[pairs[nb + be] * no + pairs[be]];
+  const zd* x = v + int64_t(blockIdx.x) * nk;
+  const zd* y = v + (int64_t(sa) * nb + be) * nk;
+  const zd* z = v + (int64_t(al) * nb + sb) * nk;
+  bool bad = false;
+  for (int k = threadIdx.x; k < nk; k += 256) {
+    const zd a = x[k], b = y[k], c = z[k];
+    bad |= !(a.re == b.re && a.im == b.im && a.re == c.re && a.im == c.im);
+  }
+  if (bad) atomicOr(flag, 1);
+}
+
+// gather of the representatives' entries: out[m][u][v] = in[m][rep(u)][rep(v)]
+__global__ __launch_bounds__(256) void k_fold_matrix(const zd* __restrict__ in, zd* __restrict__ out, int64_t n, int nb,
+                                                     int nf, int no, const int* __restrict__ pairs,
+                                                     const int* __restrict__ fold) {
+  const int64_t gi = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  if (gi >= n * nf * nf) return;
+  const int v = int(gi % nf), u = int((gi / nf) % nf);
+  const int64_t m = gi / (int64_t(nf) * nf);
+  const int* of = pairs + 2 * nb;
+  out[gi] = in[(m * nb + of[fold[u] * no + fold[nf + u]]) * nb + of[fold[v] * no + fold[nf + v]]];
+}
+
+__global__ __launch_bounds__(256) void k_unfold_matrix(const zd* __restrict__ in, zd* __restrict__ out, int64_t n,
+                                                       int nb, int nf, int64_t ld, const int* __restrict__ fold) {
+  const int64_t gi = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  if (gi >= n * nb * nb) return;
+  const int b = int(gi % nb), a = int((gi / nb) % nb);
+  const int* cls = fold + 2 * nf;
+  out[gi] = in[gi / (int64_t(nb) * nb) * ld + int64_t(cls[a]) * nf + cls[b]];
+}
+
 __global__ void k_add(const zd* __restrict__ a, const zd* __restrict__ b, zd* __restrict__ out, int64_t n) {
   const int64_t gi = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (gi < n) out[gi] = a[gi] + b[gi];
@@ -388,6 +426,24 @@ hipError_t launch_slab_to_matrix_static(const Plan& p, const void* in, void* out
   const int na = p.nb * p.nb;
   const int64_t n = int64_t(na) * p.nk;
   hipLaunchKernelGGL(k_static_transpose, dim3(nblk(n, 256)), dim3(256), 0, s, (const zd*)in, (zd*)out, na, p.nk);
+  return hipGetLastError();
+}
+
+hipError_t launch_fold_check(const Plan& p, const void* v_r, int* flag, hipStream_t s) {
+  hipLaunchKernelGGL(k_fold_check, dim3(unsigned(p.nb * p.nb)), dim3(256), 0, s, (const zd*)v_r, p.nb, p.nk, p.no,
+                     p.d_pairs, flag);
+  return hipGetLastError();
+}
+
+hipError_t launch_fold_matrix(const Plan& p, int64_t n, const void* full, void* folded, hipStream_t s) {
+  hipLaunchKernelGGL(k_fold_matrix, dim3(nblk(n * p.fold_nb * p.fold_nb, 256)), dim3(256), 0, s, (const zd*)full,
+                     (zd*)folded, n, p.nb, p.fold_nb, p.no, p.d_pairs, p.d_fold_pairs);
+  return hipGetLastError();
+}
+
+hipError_t launch_unfold_matrix(const Plan& p, int64_t n, const void* folded, int64_t ld, void* full, hipStream_t s) {
+  hipLaunchKernelGGL(k_unfold_matrix, dim3(nblk(n * p.nb * p.nb, 256)), dim3(256), 0, s, (const zd*)folded, (zd*)full,
+                     n, p.nb, p.fold_nb, ld, p.d_fold_pairs);
   return hipGetLastError();
 }
 

@@ -27,6 +27,9 @@ namespace qgw {
 // Pair-basis sizes with a compiled Dyson-W solver.
 #define QGW_FOR_EACH_NB(X) X(1) X(2) X(4) X(5) X(8) X(9) X(16) X(25)
 
+// Folded pair-basis sizes (see Plan::fold_nb) with a compiled Dyson-W solver besides those above.
+#define QGW_FOR_EACH_NB_FOLDED(X) X(3) X(6) X(7) X(10) X(12) X(15)
+
 // Orbital counts with a compiled Dyson-G solver.
 #define QGW_FOR_EACH_NO(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
 
@@ -86,6 +89,15 @@ struct Plan {
   int* d_pairs = nullptr;  // [2 * nb]: first, second
   TermTable terms;     // keyed by (i, k): entries (alpha, beta, l, j)
   TermTable terms_lj;  // keyed by (l, j): entries (alpha, beta, i, k)
+  // The folded pair basis: one class per unordered pair {i, l} of a site (N_b = sum n (n + 1) / 2; 15 of 25 for five
+  // orbitals).  An interaction that does not change under i <-> l of either index, as that of real orbitals (the
+  // pair density phi_i phi_l is symmetric), factors as V = S U S^T with S the 0/1 map of pairs to classes, and then
+  // W = V + V P W has W = S Y S^T with Y = U + U (S^T P S) Y: P enters only summed over the members of its classes,
+  // and W^C has equal entries there.  A state whose V(R) has this symmetry keeps its pair arrays in this basis.
+  int fold_nb = 0;            // classes; 0 where they are as many as the pairs or have no compiled solver
+  int* d_fold_pairs = nullptr;  // [2 fold_nb] first, second of each class's representative, then [nb] class of a pair
+  TermTable fold_terms;       // the terms with the classes of alpha and beta
+  bool folded = false;        // set in fold_plan's copy: nb, d_pairs and terms are the folded basis's
   double* d_wn = nullptr;  // fermionic Matsubara frequencies (r)
   zd* d_qp_row = nullptr;  // node values -> value at i pi / beta (r)
   // Dyson-G scratch: partial sums (2 x max blocks x 4), status words ([0] search status, [8] count of
@@ -98,6 +110,17 @@ struct Plan {
   Tune tune32;              // shapes of the FP32 kernels of an FP64 plan (a state's single-precision iterations)
   bool has_tune32 = false;
 };
+
+// the plan with its pair basis replaced by the folded one (shares every device table with p)
+inline Plan fold_plan(const Plan& p) {
+  Plan f = p;
+  f.nb = p.fold_nb;
+  f.d_pairs = p.d_fold_pairs;
+  f.terms = p.fold_terms;
+  f.terms_lj = TermTable();
+  f.folded = true;
+  return f;
+}
 
 void set_error(const std::string& msg);
 
@@ -124,6 +147,7 @@ hipError_t launch_lattice_fft(const Plan& p, int dir, int64_t batch, const void*
 // the same transform of two arrays of ``batch`` slabs each, in one launch on a square mesh
 hipError_t launch_lattice_fft2(const Plan& p, int dir, int64_t batch, const void* in1, void* out1, const void* in2,
                                void* out2, hipStream_t s);
+// a folded plan's bubble is summed over the members of both classes (out_q = 1 only)
 hipError_t launch_bubble(const Plan& p, const void* g_tau_r, const void* g_reflt_r, int out_q,
                          void* out, hipStream_t s);
 hipError_t launch_sigma(const Plan& p, const void* g_tau_r, const void* wc, int in_q, int out_k,
@@ -185,6 +209,12 @@ hipError_t launch_dyson_g_chain(const Plan& p, const void* h_k, const void* sig_
                                 hipStream_t s, const double* dpart = nullptr, int dnblk = 0,
                                 const double* bmax = nullptr, int nbmax = 0, double* dsig = nullptr);
 hipError_t launch_slab_to_matrix_static(const Plan& p, const void* in, void* out, hipStream_t s);
+// *flag |= 1 where V(R) (slab layout) changes under i <-> l of a pair index (a NaN counts as a change)
+hipError_t launch_fold_check(const Plan& p, const void* v_r, int* flag, hipStream_t s);
+// folded [n][fold_nb^2] <- rows of the full pair matrices [n][N_b^2] at the classes' representatives
+hipError_t launch_fold_matrix(const Plan& p, int64_t n, const void* full, void* folded, hipStream_t s);
+// full [n][N_b^2] <- folded matrices (row stride ld), every member of a class alike
+hipError_t launch_unfold_matrix(const Plan& p, int64_t n, const void* folded, int64_t ld, void* full, hipStream_t s);
 hipError_t launch_add(const Plan& p, int64_t count, const void* a, const void* b, void* out,
                       hipStream_t s);
 // d_sigma = max |(hf_new + c_new) - (hf_old + c_old)| (non-finite entries count as +inf); then optional mixing
