@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libqgw.so")
 
-SOURCES = ["api.cpp", "dlr_host.cpp", "kernels_fft.hip", "kernels_dlr.hip", "kernels_dyson.hip",
+SOURCES = ["api.cpp", "dlr_host.cpp", "kernels_fft.hip", "kernels_dlr.hip", "kernels_dyson.hip", "kernels_dyson_wq.hip",
            "kernels_misc.hip", "kernels_bwd.hip", "kernels_qp.hip", "kernels_hf.hip", "kernels_fft3.hip", "kernels_mf.hip",
            "autotune.cpp"]
 

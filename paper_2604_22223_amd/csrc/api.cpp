@@ -421,6 +421,8 @@ static qgw_status plan_create_impl(const qgw_plan_desc* d, int mf_nodes, qgw_pla
   std::vector<int> fold_pairs(ffirst), fold_terms(terms);
   fold_pairs.insert(fold_pairs.end(), fsecond.begin(), fsecond.end());
   fold_pairs.insert(fold_pairs.end(), cls.begin(), cls.end());
+  for (int a = 0; a < nb; ++a) fold_pairs.push_back(p.pair_of[size_t(p.pair_second[a]) * no + p.pair_first[a]]);
+  for (int u = 0; u < nf; ++u) fold_pairs.push_back(p.pair_of[size_t(ffirst[u]) * no + fsecond[u]]);
   for (size_t i = 0; i < fold_terms.size(); i += 4) {
     fold_terms[i] = cls[fold_terms[i]];
     fold_terms[i + 1] = cls[fold_terms[i + 1]];
@@ -1583,7 +1585,7 @@ static hipError_t enqueue_steps(qgw_state st, bool f32, bool prof, hipStream_t s
     mark(4);  // a5
     run(launch_dlr_pairs(pw, QGW_B_TAU2IW, QGW_LAYOUT_SLAB, QGW_LAYOUT_MATRIX, st->Pq, st->P_nu, s));
     mark(5);  // a6
-    run(launch_dyson_w(pw, st->V_qm, st->P_nu, st->Wc_nu, s, state_w_ld(pw)));
+    run(launch_dyson_w(pw, st->V_qm, st->P_nu, st->Wc_nu, s, state_w_ld(pw), false));
     mark(6);  // a7
     run(launch_dlr_pairs(pw, QGW_B_IW2TAU, QGW_LAYOUT_MATRIX, QGW_LAYOUT_SLAB, st->Wc_nu, st->Pq, s,
                          state_w_ld(pw)));
@@ -1601,7 +1603,7 @@ static hipError_t enqueue_steps(qgw_state st, bool f32, bool prof, hipStream_t s
     mark(4);
     run(launch_dlr_pairs(q, QGW_B_TAU2IW, QGW_LAYOUT_SLAB, QGW_LAYOUT_MATRIX, st->Pq32, st->Pnu32, s));
     mark(5);
-    run(launch_dyson_w(q, st->Vqm32, st->Pnu32, st->Wc32, s, state_w_ld(q)));
+    run(launch_dyson_w(q, st->Vqm32, st->Pnu32, st->Wc32, s, state_w_ld(q), false));
     mark(6);
     run(launch_dlr_pairs(q, QGW_B_IW2TAU, QGW_LAYOUT_MATRIX, QGW_LAYOUT_SLAB, st->Wc32, st->Pq32, s, state_w_ld(q)));
     mark(7);

@@ -148,7 +148,7 @@ qgw_status qgw_plan_autotune(qgw_plan h, int32_t* choices, void* stream) {
     });
     tn.orb_valu = code == 0 ? 0 : 1;
     tn.orb_mt = code;
-    if (q.nb == 25) pick(t, s, {0, 1}, tn.w25_mfma, [&] { return launch_dyson_w(q, vv, pa, pb, s, 0); });
+    if (q.nb == 25) pick(t, s, {0, 1}, tn.w25_mfma, [&] { return launch_dyson_w(q, vv, pa, pb, s, 0, false); });
   };
   tune_one(p);
   if (p.prec == QGW_F64) {

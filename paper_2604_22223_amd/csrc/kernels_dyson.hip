@@ -26,6 +26,7 @@
 #include <cmath>
 #include <utility>
 
+#include "qgw_gj.h"
 #include "qgw_internal.h"
 #include "qgw_mfma.h"
 
@@ -52,32 +53,6 @@ struct DysonWShape {
 template <typename T>
 __device__ __forceinline__ cpx<T> shfl_cpx(cpx<T> v, int src, int width) {
   return mk(__shfl(v.re, src, width), __shfl(v.im, src, width));
-}
-
-// row shift by DPP; a lane whose source lies outside its row gets INT_MIN, the identity of the max it feeds, so the
-// shift folds into the max instruction (no copy of the value first)
-template <int CTRL>
-__device__ __forceinline__ int dpp_shl_i(int v) {
-  return __builtin_amdgcn_update_dpp(int(0x80000000u), v, CTRL, 0xF, 0xF, false);
-}
-
-// 1 / d by the hardware estimate and Newton-Raphson steps r <- r (2 - d r)
-__device__ __forceinline__ double rcp_nr(double d) {
-  double r = __builtin_amdgcn_rcp(d);
-  double e = __builtin_fma(-d, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  e = __builtin_fma(-d, r, 1.0);
-  return __builtin_fma(r, e, r);
-}
-__device__ __forceinline__ float rcp_nr(float d) {
-  const float r = __builtin_amdgcn_rcpf(d);
-  return __builtin_fmaf(r, __builtin_fmaf(-d, r, 1.0f), r);
-}
-
-// |Re| + |Im| rounded to FP32, as bits; a larger value compares larger
-template <typename T>
-__device__ __forceinline__ int mag_bits(cpx<T> a) {
-  return __float_as_int(float(fabs(a.re) + fabs(a.im)));
 }
 
 // ADJ: solve (I - V P)^H X = B instead, with B (pair matrix layout, dense) in place of V, and write X
@@ -328,18 +303,16 @@ __device__ __forceinline__ void gj25_all(cpx<T> (&x)[3][7], cpx<T>& y, int (&cs)
 // VALU rate and the 32 x 32 x 28 padding costs 1.8x the product's flops: measured at 24 x 24, r = 53 it takes
 // 0.46 ms (FP64) and 0.27 ms (FP32) against 0.42 and 0.25 for the VALU product, so it is an autotuner
 // alternative and not the default.
-// FP32 asks for five waves per SIMD: its elimination fits 96 VGPRs without spills (97 by default, four waves)
-template <typename T, bool ADJ = false, bool MVP = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 1))) void k_dyson_w25(const cpx<T>* __restrict__ vq, const cpx<T>* __restrict__ pnu,
-                                                  cpx<T>* __restrict__ wc, int64_t nmat, int nk, int64_t ld,
-                                                  int* __restrict__ cond, const cpx<T>* __restrict__ rhs = nullptr) {
+// one matrix; xs: a chunk of P rows, then the pivot exchange; sv: V(q)
+template <typename T, bool ADJ, bool MVP>
+__device__ __forceinline__ void w25_solve(const cpx<T>* __restrict__ vq, const cpx<T>* __restrict__ pnu,
+                                          cpx<T>* __restrict__ wc, int64_t mat, int nk, int64_t ld,
+                                          int* __restrict__ cond, const cpx<T>* __restrict__ rhs, cpx<T>* xs,
+                                          cpx<T>* sv) {
   constexpr int NB = W25::NB, NN = NB * NB, NS = W25::NS, NT = W25::NT, CH = W25::CH, NCH = W25::NCH;
-  __shared__ cpx<T> xs[W25::XS];  // a chunk of P rows; then the pivot exchange
-  __shared__ cpx<T> sv[NN];       // V(q)
   const int lane = threadIdx.x;
   const int rg = lane & 7, cg = lane >> 3;
   const int c24 = cg + 8 * rg;  // this lane's column of row 24
-  const int64_t mat = blockIdx.x;
   const int q = int(mat % nk);
   const cpx<T>* vm = vq + int64_t(q) * NN;
   const cpx<T>* pm = pnu + mat * NN;
@@ -534,6 +507,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     }
   }
   if (c24 >= NB && c24 < 2 * NB) wm[k24 * NB + c24 - NB] = ADJ ? y : y - (MVP ? vm : sv)[k24 * NB + c24 - NB];
+}
+
+// FP32 asks for five waves per SIMD: its elimination fits 96 VGPRs without spills (97 by default, four waves).
+// guarded: only the matrices that the folded solver left marked
+template <typename T, bool ADJ = false, bool MVP = false>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 1))) void k_dyson_w25(
+    const cpx<T>* __restrict__ vq, const cpx<T>* __restrict__ pnu, cpx<T>* __restrict__ wc, int64_t nmat, int nk,
+    int64_t ld, int* __restrict__ cond, const cpx<T>* __restrict__ rhs = nullptr, int guarded = 0) {
+  __shared__ cpx<T> xs[W25::XS];
+  __shared__ cpx<T> sv[W25::NB * W25::NB];
+  if (guarded && !is_left_mark(wc[int64_t(blockIdx.x) * ld])) return;
+  w25_solve<T, ADJ, MVP>(vq, pnu, wc, blockIdx.x, nk, ld, cond, rhs, xs, sv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1246,30 +1231,84 @@ __global__ __launch_bounds__(64) void k_dyson_g_bwd2(DysonGArgs A, double mu, do
 // ---------------------------------------------------------------------------
 namespace {
 
+template <typename T>
+hipError_t dyson_w25(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, hipStream_t s, int64_t ld,
+                     bool guarded) {
+  const int64_t nmat = int64_t(p.r) * p.nk;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(unsigned(nmat)), dim3(64), 0, s, (const cpx<T>*)v_q, (const cpx<T>*)p_nu,
+                       (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord, nullptr, guarded ? 1 : 0);
+  };
+  if (p.tune.w25_mfma == 1)
+    go(k_dyson_w25<T, false, true>);
+  else
+    go(k_dyson_w25<T, false, false>);
+  return hipGetLastError();
+}
+
 template <int NB, typename T>
-hipError_t dyson_w_nb(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, hipStream_t s, int64_t ld) {
+hipError_t dyson_wr(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, hipStream_t s, int64_t ld) {
+  const int64_t nmat = int64_t(p.r) * p.nk;
+  hipLaunchKernelGGL((k_dyson_wr<T, NB>), dim3(unsigned(nmat)), dim3(64), 0, s, (const cpx<T>*)v_q,
+                     (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord, nullptr);
+  return hipGetLastError();
+}
+
+template <int NB, typename T>
+hipError_t dyson_w_small(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, hipStream_t s, int64_t ld) {
   constexpr int MPW = DysonWShape<NB>::MPW;
   const int64_t nmat = int64_t(p.r) * p.nk;
-  if (ld == 0) ld = int64_t(NB) * NB;
-  if (ld < int64_t(NB) * NB) return hipErrorInvalidValue;
-  if (NB == 25) {
-    if (p.tune.w25_mfma == 1)
-      hipLaunchKernelGGL((k_dyson_w25<T, false, true>), dim3(unsigned(nmat)), dim3(64), 0, s, (const cpx<T>*)v_q,
-                         (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord, nullptr);
-    else
-      hipLaunchKernelGGL((k_dyson_w25<T, false, false>), dim3(unsigned(nmat)), dim3(64), 0, s, (const cpx<T>*)v_q,
-                         (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord, nullptr);
-    return hipGetLastError();
-  }
-  if constexpr (NB > 8 && NB <= 16) {
-    hipLaunchKernelGGL((k_dyson_wr<T, NB>), dim3(unsigned(nmat)), dim3(64), 0, s, (const cpx<T>*)v_q,
-                       (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord);
-    return hipGetLastError();
-  }
-  const unsigned blocks = unsigned((nmat + MPW - 1) / MPW);
-  hipLaunchKernelGGL((k_dyson_w<NB, T>), dim3(blocks), dim3(64), 0, s, (const cpx<T>*)v_q,
-                     (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord);
+  hipLaunchKernelGGL((k_dyson_w<NB, T>), dim3(unsigned((nmat + MPW - 1) / MPW)), dim3(64), 0, s, (const cpx<T>*)v_q,
+                     (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord, nullptr);
   return hipGetLastError();
+}
+
+template <typename T>
+hipError_t dyson_w_t(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, hipStream_t s, int64_t ld,
+                     bool fold) {
+  const int64_t nn = int64_t(p.nb) * p.nb, nmat = int64_t(p.r) * p.nk;
+  if (ld == 0) ld = nn;
+  if (ld < nn) return hipErrorInvalidValue;
+  // FP32 calls on the caller's arrays keep the eliminations that follow, bit for bit: their rounding, amplified 19-56
+  // times by the i nu -> tau map behind, shows at 1e-5 in W^C(tau), so another order of the same sums is another result
+  if (sizeof(T) == 4 && fold) {
+    switch (p.nb) {
+      case 8: return dyson_w_small<8, T>(p, v_q, p_nu, wc_nu, s, ld);
+      case 9: return dyson_wr<9, T>(p, v_q, p_nu, wc_nu, s, ld);
+      case 16: return dyson_wr<16, T>(p, v_q, p_nu, wc_nu, s, ld);
+      default: fold = false;
+    }
+  }
+  // FP64, N_b >= 9: matrices whose V(q) has the pair-exchange symmetry are solved per unordered pair; the others are
+  // left marked for the general kernel behind.  24 x 24, r = 53: 234 instead of 447 us (N_b = 25), 67 instead of 163
+  // (16), 28 instead of 71 (9).  A V without the symmetry pays for the look at it, up to 8% (N_b = 16, 12 x 12: 54
+  // against 50 us); below 4,096 matrices, where the second launch costs as much as the smaller systems save (6 x 6: 23
+  // against 18 us at N_b = 16), nothing is tried.  The mark sits in the output, so an output over the input P (or V)
+  // takes the general kernel alone.
+  const auto overlap = [&](const void* x, int64_t count) {
+    const char *a = (const char*)x, *b = (const char*)wc_nu;
+    return a < b + nmat * ld * int64_t(sizeof(cpx<T>)) && b < a + count * int64_t(sizeof(cpx<T>));
+  };
+  bool guarded = false;
+  if (fold && !p.folded && p.fold_nb && p.nb >= 9 && nmat >= 4096 && !overlap(p_nu, nmat * nn) && !overlap(v_q, p.nk * nn)) {
+    const hipError_t e = launch_dyson_wq_fold(p, v_q, p_nu, wc_nu, ld, s);
+    if (e != hipSuccess) return e;
+    guarded = true;
+  }
+  if (p.nb == 25) return dyson_w25<T>(p, v_q, p_nu, wc_nu, s, ld, guarded);
+  switch (p.nb) {  // up to five pairs the two-lanes-per-row form is as fast or faster
+    case 1: return dyson_w_small<1, T>(p, v_q, p_nu, wc_nu, s, ld);
+    case 2: return dyson_w_small<2, T>(p, v_q, p_nu, wc_nu, s, ld);
+    case 3: return dyson_w_small<3, T>(p, v_q, p_nu, wc_nu, s, ld);
+    case 4: return dyson_w_small<4, T>(p, v_q, p_nu, wc_nu, s, ld);
+    case 5: return dyson_w_small<5, T>(p, v_q, p_nu, wc_nu, s, ld);
+    default: break;
+  }
+  // four matrices per wavefront; few larger ones (under six wavefronts of one matrix per SIMD) finish sooner one to a
+  // wavefront: N_b = 16 with 1,908 matrices 10.6 against 18.4 us in FP32, with 7,632 the same
+  if (p.nb >= 15 && nmat < 6000 && !guarded)
+    return p.nb == 16 ? dyson_wr<16, T>(p, v_q, p_nu, wc_nu, s, ld) : dyson_wr<15, T>(p, v_q, p_nu, wc_nu, s, ld);
+  return launch_dyson_wq(p, v_q, p_nu, wc_nu, ld, s, guarded);
 }
 
 template <int NO>
@@ -1453,19 +1492,10 @@ hipError_t launch_dyson_g_bwd(const Plan& p, const void* h_k, const void* sig_iw
   }
 }
 
-hipError_t launch_dyson_w(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu,
-                          hipStream_t s, int64_t out_ld) {
-  switch (p.nb) {
-#define QGW_CASE(NBV)                                                                     \
-  case NBV:                                                                               \
-    return p.prec == 0 ? dyson_w_nb<NBV, double>(p, v_q, p_nu, wc_nu, s, out_ld)          \
-                       : dyson_w_nb<NBV, float>(p, v_q, p_nu, wc_nu, s, out_ld);
-    QGW_FOR_EACH_NB(QGW_CASE)
-    QGW_FOR_EACH_NB_FOLDED(QGW_CASE)
-#undef QGW_CASE
-    default:
-      return hipErrorInvalidValue;
-  }
+hipError_t launch_dyson_w(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, hipStream_t s,
+                          int64_t out_ld, bool fold) {
+  return p.prec == 0 ? dyson_w_t<double>(p, v_q, p_nu, wc_nu, s, out_ld, fold)
+                     : dyson_w_t<float>(p, v_q, p_nu, wc_nu, s, out_ld, fold);
 }
 
 #define QGW_NO_SWITCH(CALL)    \

@@ -30,6 +30,12 @@ namespace qgw {
 // Folded pair-basis sizes (see Plan::fold_nb) with a compiled Dyson-W solver besides those above.
 #define QGW_FOR_EACH_NB_FOLDED(X) X(3) X(6) X(7) X(10) X(12) X(15)
 
+// Sizes whose Dyson-W solver takes four matrices per wavefront.
+#define QGW_FOR_EACH_NB_WQ(X) X(6) X(7) X(8) X(9) X(10) X(12) X(15) X(16)
+
+// Full and folded sizes (N_b >= 9) whose full matrices are solved through the folded basis.
+#define QGW_FOR_EACH_FOLD(X) X(25, 15) X(25, 16) X(16, 10) X(16, 12) X(9, 6) X(9, 7)
+
 // Orbital counts with a compiled Dyson-G solver.
 #define QGW_FOR_EACH_NO(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
 
@@ -93,9 +99,12 @@ struct Plan {
   // orbitals).  An interaction that does not change under i <-> l of either index, as that of real orbitals (the
   // pair density phi_i phi_l is symmetric), factors as V = S U S^T with S the 0/1 map of pairs to classes, and then
   // W = V + V P W has W = S Y S^T with Y = U + U (S^T P S) Y: P enters only summed over the members of its classes,
-  // and W^C has equal entries there.  A state whose V(R) has this symmetry keeps its pair arrays in this basis.
+  // and W^C has equal entries there.  A state whose V(R) has this symmetry (V is
+  // compared entry by entry) keeps its pair arrays in this basis: five orbitals, 24 x 24, r = 53, FP64, the pair maps
+  // take 95 and 92 us each instead of 236 and 218, Dyson W 118 instead of 425.
   int fold_nb = 0;            // classes; 0 where they are as many as the pairs or have no compiled solver
-  int* d_fold_pairs = nullptr;  // [2 fold_nb] first, second of each class's representative, then [nb] class of a pair
+  int* d_fold_pairs = nullptr;  // [2 fold_nb] first, second of each class's representative, then [nb] class of a
+                                // pair, [nb] its exchanged partner, [fold_nb] pair index of the representative
   TermTable fold_terms;       // the terms with the classes of alpha and beta
   bool folded = false;        // set in fold_plan's copy: nb, d_pairs and terms are the folded basis's
   double* d_wn = nullptr;  // fermionic Matsubara frequencies (r)
@@ -161,9 +170,16 @@ hipError_t launch_dlr2(const Plan& p, int map1, int map2, int64_t ncols, const v
 // in_ld: row stride (elements) of a matrix-layout input, 0 for N_b^2 (only the matrix-core path takes another)
 hipError_t launch_dlr_pairs(const Plan& p, int map, int in_layout, int out_layout, const void* in,
                             void* out, hipStream_t s, int64_t in_ld = 0);
-// out_ld: row stride (elements) of the W^C matrices written, 0 for N_b^2
+// out_ld: row stride (elements) of the W^C matrices written, 0 for N_b^2; fold = false: V is known to lack the
+// pair-exchange symmetry at some q (or the general kernel is to be timed)
 hipError_t launch_dyson_w(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu,
-                          hipStream_t s, int64_t out_ld = 0);
+                          hipStream_t s, int64_t out_ld = 0, bool fold = true);
+// the form with four matrices per wavefront (kernels_dyson_wq.hip)
+hipError_t launch_dyson_wq(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, int64_t ld, hipStream_t s,
+                           int guarded);
+// full matrices through the folded basis where V(q) allows it; the other matrices are marked (qgw_gj.h)
+hipError_t launch_dyson_wq_fold(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, int64_t ld,
+                                hipStream_t s);
 // row stride of the W^C matrices a state keeps: rounded up to 128-byte lines (16 complex FP32 values) when the
 // matrix-core pair maps read them, so that the matrix -> slab map reads whole lines
 inline int64_t state_w_ld(const Plan& p) {

@@ -62,3 +62,75 @@ def test_state_in_the_folded_basis(site_norb, dim, symmetric):
     assert st.iterate(5, tol=1e6)[0] == 1
     assert rel_err(host(3), matrix(s2["intermediates"]["P_nu_q"], dim)) < TOL
     assert rel_err(host(1), flat(s2["sig_iw"], dim)) < TOL
+
+
+def fold_v(rng, nk, site_norb):
+    """Hermitian V(q) unchanged under i <-> l of either index (random values per class pair)."""
+    first, second, off = [], [], 0
+    for n in site_norb:
+        for i in range(n):
+            for l in range(n):
+                first.append(off + min(i, l))
+                second.append(off + max(i, l))
+        off += n
+    cls = {}
+    idx = np.array([cls.setdefault(k, len(cls)) for k in zip(first, second)])
+    v = rng.standard_normal((nk, len(cls), len(cls))) + 1j * rng.standard_normal((nk, len(cls), len(cls)))
+    v = 0.1 * (v + np.conj(np.swapaxes(v, 1, 2))) + 0.5 * np.eye(len(cls))
+    return np.ascontiguousarray(v[:, idx][:, :, idx])
+
+
+# every compiled (N_b, classes) pair of the folded solver; ranks of every remainder modulo four nodes per wavefront, on
+# a mesh that puts the matrices above the 4,096 from which the folded solver runs
+@pytest.mark.parametrize("site_norb", [[5], [4, 3], [4], [2, 2, 2, 2], [3], [2, 2, 1]], ids=str)
+@pytest.mark.parametrize("rank", [4, 5, 6, 7])
+@pytest.mark.parametrize("mixed", [False, True], ids=["symmetric", "some_q_not"])
+def test_dyson_w_of_a_foldable_interaction(site_norb, rank, mixed):
+    n = 32
+    nk = n * n
+    rng = np.random.default_rng(5 + rank)
+    nodes = dict(omega=np.linspace(-1.0, 1.0, rank), tau_t=np.linspace(0.1, 0.9, rank), n_f=np.arange(rank) - rank // 2,
+                 n_b=np.arange(rank) - rank // 2)
+    p = qgw.Plan.from_nodes(n, site_norb, 3.0, nodes)
+    nb = p.n_b
+    v = fold_v(rng, nk, site_norb)
+    if mixed:  # one entry of one index at some q
+        v[1, 1, 0] += 0.1
+        v[4, 0, 1] += 0.1
+    pnu = 0.05 * (rng.standard_normal((rank, nk, nb, nb)) + 1j * rng.standard_normal((rank, nk, nb, nb)))
+    vd, pd = dev(v), dev(pnu)
+    out = torch.empty_like(pd)
+    print("\n[fold] Dyson W %s, rank %d" % (site_norb, rank), flush=True)
+    p.dyson_W(vd, pd, out)
+    p.sync_status()
+    some = np.unique(np.concatenate([[0, 1, 4, nk - 1], rng.integers(0, nk, 40)]))  # the q compared
+    v64, p64 = v[some], pnu[:, some]
+    ref = np.linalg.solve(np.eye(nb) - v64[None] @ p64, np.broadcast_to(v64[None], p64.shape)) - v64[None]
+    assert rel_err(out.cpu().numpy()[:, some], ref) < TOL
+    p.dyson_W(vd, pd, pd)  # the output over P: the general kernel alone
+    assert rel_err(pd.cpu().numpy()[:, some], ref) < TOL
+    p.close()
+
+
+@pytest.mark.parametrize("site_norb", [[5], [4], [3]], ids=str)
+def test_singular_system_of_a_foldable_interaction_is_reported(site_norb):
+    """I - V P with a zero row and column in the folded basis: the status word, and non-finite entries there only."""
+    n, rank = 32, 5
+    nodes = dict(omega=np.linspace(-1.0, 1.0, rank), tau_t=np.linspace(0.1, 0.9, rank), n_f=np.arange(rank) - 2,
+                 n_b=np.arange(rank) - 2)
+    p = qgw.Plan.from_nodes(n, site_norb, 3.0, nodes)
+    nb, nk = p.n_b, p.n_k
+    v = np.zeros((nk, nb, nb), dtype=complex)
+    v[:, 0, 0] = 2.0
+    pnu = np.zeros((rank, nk, nb, nb), dtype=complex)
+    pnu[3, 1, 0, 0] = 0.5
+    out = torch.empty((rank, nk, nb, nb), dtype=torch.complex128, device="cuda:0")
+    p.dyson_W(dev(v), dev(pnu), out)
+    with pytest.raises(qgw.QGWError) as e:
+        p.sync_status()
+    assert e.value.status == qgw.QGW_ERR_SINGULAR
+    got = out.cpu().numpy()
+    assert not np.all(np.isfinite(got[3, 1]))
+    got[3, 1] = 0.0
+    assert np.all(got == 0.0)
+    p.close()
