@@ -364,35 +364,58 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 }
 
 // Pair arrays with the slab <-> matrix layout change.  A block of 8 waves
-// takes a tile of 16 x 8 columns: 16 values of the index L that is contiguous
-// in the output (one per lane of a strip) and 8 values of the index W that is
-// contiguous in the input (one per wave).  Per 4-deep slice of the node axis
-// the block reads the 4 x 16 x 8 input values with one load per thread (eight
-// threads cover 128 contiguous bytes), issued a slice ahead, and passes them
+// takes a tile of 16 x 8 WT columns: 16 values of the index L that is contiguous
+// in the output (one per lane of a strip) and 8 WT values of the index W that is
+// contiguous in the input (WT per wave; WT = 1 in FP64 and 2 in FP32, so that a row of the tile is a whole 128-byte
+// line).  Per 4-deep slice of the node axis the block reads the input values with WT loads per thread, issued a slice
+// ahead (the last slice of a tile reads the first of the next), and passes them
 // through LDS (two buffers, alternating by slice); each wave then multiplies
-// its 16-column strip on the matrix cores and writes whole 16-value runs of
+// its strips on the matrix cores and writes whole 16-value runs of
 // the output.  Slab -> matrix: L = pair index a, W = q; matrix -> slab:
 // L = q, W = a.
-// WT: W values per wave (tile 16 x 8 WT).  FP32 takes WT = 2, so that the eight threads' values of one row of the
-// input (8 WT x 8 bytes) are a whole 128-byte line, as the 8 FP64 values of WT = 1 are; each barrier then also
-// carries twice the matrix-core work.
+// A wave that has its operands goes first on its SIMD (s_setprio around the products), so the waves of a SIMD stay out
+// of step and the barriers of one block overlap the products of the other: five orbitals, 24 x 24, r = 53, a5 and a7
+// 226 and 211 -> 217 and 199 us in FP64, 150 and 128 -> 127 and 114 in FP32 (the same sums, bit for bit).  Two or
+// four slices per barrier, one block of 16 waves per CU, and operands loaded straight into the matrix-core layout
+// with the output turned through LDS all measured slower (FP64 227-253 us for a5).
 template <typename T, int MT, int MODE, int WT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_dlr_mfma_pairs(
     const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, const cpx<T>* __restrict__ map, int r, int kp,
-    int na, int nq, int tiles_l, int64_t ntiles, T sre, T sim, int64_t in_ld) {
+    int na, int nq, int tiles_l, int ntiles, T sre, T sim, int64_t in_ld) {
   using M = Mfma<T>;
   using v4 = typename M::v4;
-  constexpr int TW = 8 * WT;         // W extent of a tile
+  constexpr int TW = 8 * WT;           // W extent of a tile
   constexpr int SW = WT == 2 ? 4 : 3;  // log2(TW)
-  constexpr int WP = TW + 1;         // padded W extent of the LDS tile
-  constexpr int XT = 4 * 16 * WP;    // one tile buffer (complex values)
+  constexpr int WP = TW + 1;           // padded W extent of the LDS tile
+  constexpr int XT = 4 * 16 * WP;      // one slice buffer (complex values)
   extern __shared__ unsigned char smem_raw[];
   T* tre = reinterpret_cast<T*>(smem_raw);
   T* tim = tre + MT * 16 * kp;
   cpx<T>* xt = reinterpret_cast<cpx<T>*>(tim + MT * 16 * kp);
+  // the values this thread loads per slice (j < WT): node lt + j DT, column (lL, lW) of the tile
+  const int lW = threadIdx.x & (TW - 1), lL = (threadIdx.x >> SW) & 15, lt = threadIdx.x >> (SW + 4);
+  constexpr int DT = 512 >> (SW + 4);
+  const int nL = MODE == kSlabToMatrix ? na : nq, nW = MODE == kSlabToMatrix ? nq : na;
+  const int64_t plane = int64_t(na) * nq;
+  // the input's rows (index L) are in_ld apart, its node planes nL in_ld (in_ld >= nW: padded rows)
+  const int64_t in_plane = int64_t(nL) * in_ld;
+  // input column of this thread's loads in a tile (clamped into the array: values outside it feed only columns that
+  // are not stored)
+  auto column = [&](int t) -> const cpx<T>* {
+    const int tW = t / tiles_l, tL = t - tW * tiles_l;
+    return in + int64_t(min(tL * 16 + lL, nL - 1)) * in_ld + min(tW * TW + lW, nW - 1);
+  };
+  // node index clamped to r - 1: the map's zero padding cancels it
+  auto gload = [&](const cpx<T>* src, int kb, int j) -> cpx<T> {
+    return src[int64_t(min(kb + lt + j * DT, r - 1)) * in_plane];
+  };
+  const cpx<T>* src = column(blockIdx.x);
+  cpx<T> g[WT];
+#pragma unroll
+  for (int j = 0; j < WT; ++j) g[j] = gload(src, 0, j);
   for (int e = threadIdx.x; e < MT * 16 * kp; e += blockDim.x) {
-    const int l = e & 63, g = e >> 6;
-    const int kk = g / MT, mt = g - kk * MT;
+    const int l = e & 63, gg = e >> 6;
+    const int kk = gg / MT, mt = gg - kk * MT;
     const int i = mt * 16 + (l & 15), k = 4 * kk + (l >> 4);
     const cpx<T> v = (i < r && k < r) ? map[int64_t(i) * r + k] : mk(T(0), T(0));
     tre[e] = v.re;
@@ -400,25 +423,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lc = lane & 15, lk = lane >> 4;
-  // the values this thread loads per slice (j < WT): node lt[j], column (lL, lW) of the tile, from the index
-  // threadIdx.x + 512 j over (node, L, W) with W fastest
-  const int lW = threadIdx.x & (TW - 1), lL = (threadIdx.x >> SW) & 15;
-  int lt[WT];
-#pragma unroll
-  for (int j = 0; j < WT; ++j) lt[j] = (threadIdx.x + 512 * j) >> (SW + 4);
-  const int nL = MODE == kSlabToMatrix ? na : nq, nW = MODE == kSlabToMatrix ? nq : na;
-  const int64_t plane = int64_t(na) * nq;
-  // the input's rows (index L) are in_ld apart, its node planes nL in_ld (in_ld >= nW: padded rows)
-  const int64_t in_plane = int64_t(nL) * in_ld;
   int buf = 0;  // slice parity, continued across tiles
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int tL = int(tile % tiles_l), tW = int(tile / tiles_l);
-    // input column of this thread's loads (clamped into the array: values
-    // outside it feed only columns that are not stored)
-    const int Lld = min(tL * 16 + lL, nL - 1), Wld = min(tW * TW + lW, nW - 1);
-    const cpx<T>* src = in + int64_t(Lld) * in_ld + Wld;
-    // node index clamped to r - 1: the map's zero padding cancels it
-    auto gload = [&](int kb, int j) -> cpx<T> { return src[int64_t(min(kb + lt[j], r - 1)) * in_plane]; };
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int tW = tile / tiles_l, tL = tile - tW * tiles_l;
+    // the last slice of a tile reads the first of the next one ahead
+    const bool more = tile + int(gridDim.x) < ntiles;
+    const cpx<T>* next = more ? column(tile + gridDim.x) : src;
     const int Lo = tL * 16 + lc;
     v4 accr[WT][MT], acci[WT][MT];
 #pragma unroll
@@ -428,16 +438,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
         accr[w][mt] = v4{T(0), T(0), T(0), T(0)};
         acci[w][mt] = v4{T(0), T(0), T(0), T(0)};
       }
-    cpx<T> g[WT];
-#pragma unroll
-    for (int j = 0; j < WT; ++j) g[j] = dpp_identity(gload(0, j));
     for (int kb = 0; kb < kp; kb += 4, buf ^= 1) {
       cpx<T>* xb = xt + buf * XT;
 #pragma unroll
-      for (int j = 0; j < WT; ++j) xb[(lt[j] * 16 + lL) * WP + lW] = g[j];
+      for (int j = 0; j < WT; ++j) xb[((lt + j * DT) * 16 + lL) * WP + lW] = g[j];
       __syncthreads();  // the slice is in LDS; the buffer written next was read two slices ago
+      const bool last = kb + 4 >= kp;
+      if (!last || more) {
 #pragma unroll
-      for (int j = 0; j < WT; ++j) g[j] = gload(kb + 4, j);
+        for (int j = 0; j < WT; ++j) g[j] = gload(last ? next : src, last ? 0 : kb + 4, j);
+      }
       cpx<T> x[WT];
 #pragma unroll
       for (int w = 0; w < WT; ++w) x[w] = xb[(lk * 16 + lc) * WP + wave + 8 * w];
@@ -448,6 +458,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
         ar[mt] = tre[(kk * MT + mt) * 64 + lane];
         ai[mt] = tim[(kk * MT + mt) * 64 + lane];
       }
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int w = 0; w < WT; ++w)
 #pragma unroll
@@ -462,6 +473,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
           accr[w][mt] = M::mac(-ai[mt], x[w].im, accr[w][mt]);
           acci[w][mt] = M::mac(ai[mt], x[w].re, acci[w][mt]);
         }
+      __builtin_amdgcn_s_setprio(0);
     }
     const cpx<T> sc = mk(sre, sim);
 #pragma unroll
@@ -478,6 +490,55 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
           }
       }
     }
+    src = next;
+  }
+}
+
+// The same for few columns, where the blocks above would have at most one tile each and a barrier and a load latency
+// per slice: a wave takes 16 columns (8 values of the input's contiguous index I by 2 of the output's, O) and one
+// 16-row tile of the map, and reads all its nodes at once, straight into the operand layout; a block's waves share the
+// row tile, of which it keeps only its own 16 rows in LDS.
+template <typename T, int MODE, int SL>
+__global__ __launch_bounds__(256) void k_dlr_mfma_pairs_small(const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
+                                                              const cpx<T>* __restrict__ map, int r, int na, int nq,
+                                                              int tiles_i, int ntiles, T sre, T sim, int64_t in_ld) {
+  using M = Mfma<T>;
+  using v4 = typename M::v4;
+  __shared__ T tre[SL * 64], tim[SL * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lc = lane & 15, lk = lane >> 4;
+  const int nI = MODE == kSlabToMatrix ? nq : na, nO = MODE == kSlabToMatrix ? na : nq;
+  const int64_t plane = int64_t(na) * nq, in_plane = int64_t(nO) * in_ld;
+  const int tile = blockIdx.x * 4 + wave, mt = blockIdx.y;
+  const int tO = tile / tiles_i, tI = tile - tO * tiles_i;
+  const int I = tI * 8 + (lc & 7), O = tO * 2 + (lc >> 3);
+  // clamped into the array: columns outside it are not stored, nodes past r meet the map's zero padding
+  const cpx<T>* src = in + int64_t(min(O, nO - 1)) * in_ld + min(I, nI - 1);
+  cpx<T> x[SL];
+#pragma unroll
+  for (int s = 0; s < SL; ++s) x[s] = src[int64_t(min(4 * s + lk, r - 1)) * in_plane];
+  for (int e = threadIdx.x; e < SL * 64; e += 256) {
+    const int i = mt * 16 + (e & 15), k = 4 * (e >> 6) + ((e >> 4) & 3);
+    const cpx<T> v = (i < r && k < r) ? map[int64_t(i) * r + k] : mk(T(0), T(0));
+    tre[e] = v.re;
+    tim[e] = v.im;
+  }
+  __syncthreads();
+  v4 accr = v4{T(0), T(0), T(0), T(0)}, acci = accr;
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    const T ar = tre[s * 64 + lane], ai = tim[s * 64 + lane];
+    accr = M::mac(ar, x[s].re, accr);
+    acci = M::mac(ar, x[s].im, acci);
+    accr = M::mac(-ai, x[s].im, accr);
+    acci = M::mac(ai, x[s].re, acci);
+  }
+  if (tile >= ntiles || I >= nI || O >= nO) return;
+  const cpx<T> sc = mk(sre, sim);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int m = mt * 16 + M::row(lane, v);
+    if (m < r) out[int64_t(m) * plane + int64_t(I) * nO + O] = sc * mk(accr[v], acci[v]);
   }
 }
 
@@ -491,16 +552,39 @@ hipError_t dlr_mfma_pairs_launch(const Plan& p, int map, int na, int nq, double 
   if (in_ld == 0) in_ld = nW;
   if (in_ld < nW) return hipErrorInvalidValue;
   constexpr int WT = sizeof(T) == 4 ? 2 : 1;  // W values per wave (see the kernel)
+  constexpr int TW = 8 * WT;
   const int tiles_l = (nL + 15) / 16;
-  const int64_t ntiles = int64_t(tiles_l) * ((nW + 8 * WT - 1) / (8 * WT));
+  const int64_t nt = int64_t(tiles_l) * ((nW + TW - 1) / TW);
+  if (nt >= (int64_t(1) << 30)) return hipErrorInvalidValue;
+  const int ntiles = int(nt);
   int dev = 0, ncu = 0;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  const cpx<T>* mp = map_ptr<T>(p, map);
+  // up to 96 columns per CU: at N_b = 2, 12 x 12 (576 columns) 20 -> 8 us; at N_b = 16, 9 x 9 (20,736) 25 -> 21-25 us in
+  // FP64, 24-26 -> 14-16 in FP32; at N_b = 9, 24 x 24 (46,656) it takes 51-56 us against 39-41
+  if (int64_t(na) * nq <= int64_t(96) * ncu) {
+    const int tiles_i = (nW + 7) / 8, nts = tiles_i * ((nL + 1) / 2);
+    const dim3 grid(unsigned((nts + 3) / 4), unsigned(mt));
+#define QGW_SMALL_SL(SLV)                                                                                      \
+  case SLV:                                                                                                    \
+    hipLaunchKernelGGL((k_dlr_mfma_pairs_small<T, MODE, SLV>), grid, dim3(256), 0, s, (const cpx<T>*)in,       \
+                       (cpx<T>*)out, mp, p.r, na, nq, tiles_i, nts, T(sre), T(sim), in_ld);                    \
+    return hipGetLastError();
+    switch ((kp / 4 + 3) / 4 * 4) {
+      QGW_SMALL_SL(4)
+      QGW_SMALL_SL(8)
+      QGW_SMALL_SL(12)
+      QGW_SMALL_SL(16)
+      default:
+        return hipErrorInvalidValue;
+    }
+#undef QGW_SMALL_SL
+  }
   const int bpc = p.tune.mfma_bpc > 0 ? p.tune.mfma_bpc : 2;
   int64_t blocks = ntiles;
   if (blocks > int64_t(bpc) * ncu) blocks = int64_t(bpc) * ncu;
-  const size_t lds = size_t(2) * mt * 16 * kp * sizeof(T) + size_t(2) * 4 * 16 * (8 * WT + 1) * sizeof(cpx<T>);
-  const cpx<T>* mp = map_ptr<T>(p, map);
+  const size_t lds = size_t(2) * mt * 16 * kp * sizeof(T) + size_t(2) * 4 * 16 * (TW + 1) * sizeof(cpx<T>);
 #define QGW_MFMA_MT(MTV)                                                                                       \
   case MTV:                                                                                                    \
     hipLaunchKernelGGL((k_dlr_mfma_pairs<T, MTV, MODE, WT>), dim3(unsigned(blocks)), dim3(512), lds, s,        \
