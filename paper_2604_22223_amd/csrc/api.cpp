@@ -702,8 +702,8 @@ static qgw_status run_dyson_g(const Plan& p, const void* H_k, const void* Sig_iw
     part = p.d_partials;
     stat = p.d_status;
   }
-  // with pinned words (h_io[0..9] result, h_io[16..17] start point) the copies need no staging
-  // buffer and the host polls an event for the result instead of blocking on the stream
+  // with pinned words the final pass writes the result there itself (h_io[0..9]), and the host polls an event for it
+  // instead of blocking on the stream
   double sc_pageable[2] = {*mu, n_target};
   double* sc = sc_pageable;
   if (h_io) {
@@ -733,11 +733,11 @@ static qgw_status run_dyson_g(const Plan& p, const void* H_k, const void* Sig_iw
     const int steps = mode == 1 ? (round == 0 ? steps0 : 16) : 0;
     if (mode == 1)
       QGW_CHECK_HIP(launch_dyson_g_steps(p, H_k, Sig_iw, scal, part, stat, steps, s), "qgw_dyson_G");
-    QGW_CHECK_HIP(launch_dyson_g_final(p, H_k, Sig_iw, mode, G_iw, scal, part, stat, s, extra_src, steps),
+    QGW_CHECK_HIP(launch_dyson_g_final(p, H_k, Sig_iw, mode, G_iw, scal, part, stat, s, extra_src, steps, nullptr,
+                                       h_io),
                   "qgw_dyson_G");
     if (end_ev) QGW_CHECK_HIP(hipEventRecord(end_ev, s), "qgw_dyson_G");
     if (h_io) {
-      QGW_CHECK_HIP(hipMemcpyAsync(h_io, scal, sizeof(res), hipMemcpyDeviceToHost, s), "qgw_dyson_G");
       QGW_CHECK_HIP(hipEventRecord(io_ev, s), "qgw_dyson_G");
       // work the caller queues behind the read-back (on_queued), so the GPU has it while the host waits
       if (round == 0 && on_queued) on_queued(on_ctx);
@@ -1120,23 +1120,28 @@ qgw_status qgw_state_hf_solve(qgw_state st, double tol, int32_t max_iter, int32_
   QGW_CHECK_HIP(launch_hf_density(p, st->H_k, st->d_scal, st->d_stat, u, eps, st->n_k, s), "qgw_state_hf_solve");
   double res[4] = {};
   double dsig = NAN;
-  int bad = 0, done = 0;
+  int done = 0;
+  st->h_io[11] = st->h_io[12] = 0.0;  // nothing of this state is in flight: every earlier call waited for its words
   for (int it = 0; it < max_iter; ++it) {
     // SigH + SigF from n, the change and mixing, H = H0 + Sigma_HF, then mu and n (H class)
     QGW_CHECK_HIP(launch_lattice_fft(p, QGW_K_TO_R, int64_t(p.no) * p.no, st->n_k, st->n_R, s), "qgw_state_hf_solve");
     QGW_CHECK_HIP(launch_hartree_fock(p, st->V_R, st->V_q0, st->n_R, st->SigHF_R, s), "qgw_state_hf_solve");
     QGW_CHECK_HIP(launch_lattice_fft(p, QGW_R_TO_K, int64_t(p.no) * p.no, st->SigHF_R, st->SigHF_k, s),
                   "qgw_state_hf_solve");
-    QGW_CHECK_HIP(launch_hf_delta_mix(p, st->SigHF_k, st->SigHF_old, st->mixing, st->d_dsig, s), "qgw_state_hf_solve");
-    QGW_CHECK_HIP(launch_add(p, so_n, st->H_k, st->SigHF_k, st->Hs_k, s), "qgw_state_hf_solve");
-    QGW_CHECK_HIP(launch_hf_density(p, st->Hs_k, st->d_scal, st->d_stat, u, eps, st->n_k, s), "qgw_state_hf_solve");
-    QGW_CHECK_HIP(hipMemcpyAsync(&dsig, st->d_dsig, sizeof(double), hipMemcpyDeviceToHost, s), "qgw_state_hf_solve");
-    QGW_CHECK_HIP(hipMemcpyAsync(res, st->d_scal, sizeof(res), hipMemcpyDeviceToHost, s), "qgw_state_hf_solve");
-    QGW_CHECK_HIP(hipMemcpyAsync(&bad, st->d_stat, sizeof(int), hipMemcpyDeviceToHost, s), "qgw_state_hf_solve");
-    QGW_CHECK_HIP(hipStreamSynchronize(s), "qgw_state_hf_solve");
+    QGW_CHECK_HIP(launch_hf_mix(p, st->SigHF_k, st->SigHF_old, st->mixing, st->H_k, st->Hs_k, st->d_blockmax, s),
+                  "qgw_state_hf_solve");
+    QGW_CHECK_HIP(launch_hf_density(p, st->Hs_k, st->d_scal, st->d_stat, u, eps, st->n_k, s, st->d_blockmax, st->h_io),
+                  "qgw_state_hf_solve");
     ++done;
-    QGW_REQUIRE(bad == 0, QGW_ERR_NONFINITE, "qgw_state_hf_solve: non-finite chemical potential or filling");
-    QGW_REQUIRE(std::isfinite(dsig), QGW_ERR_NONFINITE, "qgw_state_hf_solve: non-finite Hartree-Fock self-energy");
+    // a negative tolerance asks for every pass, so the host looks only at the last (and now and then, to keep the
+    // queue short); a pass that went non-finite has left its mark in h_io[11] or [12]
+    if (tol < 0.0 && it + 1 < max_iter && (it + 1) % 64 != 0) continue;
+    QGW_CHECK_HIP(hipStreamSynchronize(s), "qgw_state_hf_solve");
+    for (int i = 0; i < 4; ++i) res[i] = st->h_io[i];
+    dsig = st->h_io[9];
+    QGW_REQUIRE(st->h_io[11] == 0.0, QGW_ERR_NONFINITE,
+                "qgw_state_hf_solve: non-finite chemical potential or filling");
+    QGW_REQUIRE(st->h_io[12] == 0.0, QGW_ERR_NONFINITE, "qgw_state_hf_solve: non-finite Hartree-Fock self-energy");
     if (dsig <= tol) break;
   }
   if (done == 0) {
@@ -1148,7 +1153,8 @@ qgw_status qgw_state_hf_solve(qgw_state st, double tol, int32_t max_iter, int32_
   QGW_CHECK_HIP(hipMemsetAsync(st->Sig_iw, 0, so * p.r, s), "qgw_state_hf_solve");
   QGW_CHECK_HIP(hipMemsetAsync(st->Sig_iw_old, 0, so * p.r, s), "qgw_state_hf_solve");
   QGW_CHECK_HIP(launch_add(p, so_n, st->H_k, st->SigHF_k, st->Hs_k, s), "qgw_state_hf_solve");
-  QGW_CHECK_HIP(launch_dyson_g_final(p, st->Hs_k, nullptr, 0, st->G_iw, st->d_scal, st->d_part, st->d_stat, s),
+  QGW_CHECK_HIP(launch_dyson_g_final(p, st->Hs_k, nullptr, 0, st->G_iw, st->d_scal, st->d_part, st->d_stat, s, nullptr,
+                                     0, nullptr, st->h_io),
                 "qgw_state_hf_solve");
   // the next GW search starts from the HF mu: no shift from a mean level of before the HF solve
   const double nan_word = NAN;
@@ -1804,8 +1810,10 @@ qgw_status qgw_batch_create(int32_t n, const qgw_state* states, int32_t precisio
   if (precision == 1)
     for (int i = 0; i < n; ++i) QGW_CHECK_HIP(ensure_fp32(states[i]), "qgw_batch_create: single-precision buffers");
   // the sticky failure words start clear (earlier eager searches may have raised them between their rounds)
-  for (int i = 0; i < n; ++i)
+  for (int i = 0; i < n; ++i) {
     QGW_CHECK_HIP(hipMemset(states[i]->d_stat + 1, 0, sizeof(int)), "qgw_batch_create");
+    states[i]->h_io[10] = 0.0;
+  }
   qgw_batch b = new (std::nothrow) qgw_batch_s;
   QGW_REQUIRE(b, QGW_ERR_ALLOC, "qgw_batch_create: out of host memory");
   b->states.assign(states, states + n);
@@ -1852,7 +1860,8 @@ qgw_status qgw_batch_create(int32_t n, const qgw_state* states, int32_t precisio
         if (ce == hipSuccess)
           ce = launch_dyson_g_chain(p, st->Hs_k, st->Sig_iw, std::isnan(st->n_target) ? 0 : 1, st->G_iw, st->d_scal,
                                     st->d_part, st->d_stat, mu_steps, st->d_stat + 1, ws, st->d_blockmax + 4096,
-                                    dyson_g_diag_blocks(p), st->d_blockmax, dyson_g_diag_blocks(p), st->d_dsig);
+                                    dyson_g_diag_blocks(p), st->d_blockmax, dyson_g_diag_blocks(p), st->d_dsig,
+                                    st->h_io);
       }
     for (int w = 0; w < nw && ce == hipSuccess; ++w) {
       ce = hipEventRecord(b->events[w], b->workers[w]);
@@ -1885,27 +1894,30 @@ qgw_status qgw_batch_read(qgw_batch b, double* d_sigma, double* mu, int32_t* sta
   QGW_REQUIRE(b, QGW_ERR_INVALID_ARG, "qgw_batch_read: null batch");
   QGW_CHECK_HIP(enter_device(b->device), "hipSetDevice");
   hipStream_t s = (hipStream_t)stream;
-  const size_t n = b->states.size();
-  std::vector<double> ds(n), m(n), ev(n);
-  std::vector<int> stt(n);
-  const int zero = 0;
-  for (size_t i = 0; i < n; ++i) {
-    qgw_state st = b->states[i];
-    QGW_CHECK_HIP(hipMemcpyAsync(&ds[i], st->d_dsig, sizeof(double), hipMemcpyDeviceToHost, s), "qgw_batch_read");
-    QGW_CHECK_HIP(hipMemcpyAsync(&m[i], st->d_scal, sizeof(double), hipMemcpyDeviceToHost, s), "qgw_batch_read");
-    QGW_CHECK_HIP(hipMemcpyAsync(&ev[i], st->d_scal + 2, sizeof(double), hipMemcpyDeviceToHost, s), "qgw_batch_read");
-    // the sticky word: the worst search status of every replay since the last read
-    QGW_CHECK_HIP(hipMemcpyAsync(&stt[i], st->d_stat + 1, sizeof(int), hipMemcpyDeviceToHost, s), "qgw_batch_read");
-    QGW_CHECK_HIP(hipMemcpyAsync(st->d_stat + 1, &zero, sizeof(int), hipMemcpyHostToDevice, s), "qgw_batch_read");
-  }
+  // each state's final pass has left mu, the evaluations, |Delta Sigma| and its sticky status word (the worst search
+  // status of every replay since the last read) in the state's pinned words
   QGW_CHECK_HIP(hipStreamSynchronize(s), "qgw_batch_read");
-  for (size_t i = 0; i < n; ++i) {
-    b->states[i]->mu = m[i];
-    if (stt[i] != 0) b->states[i]->broken = true;
-    if (d_sigma) d_sigma[i] = ds[i];
-    if (mu) mu[i] = m[i];
-    if (status) status[i] = stt[i];
-    if (evals) evals[i] = int32_t(ev[i]);
+  bool clear = false;
+  for (size_t i = 0; i < b->states.size(); ++i) {
+    qgw_state st = b->states[i];
+    const double* w = st->h_io;
+    st->mu = w[0];
+    if (int(w[10]) != 0) {
+      st->broken = true;
+      clear = true;
+    }
+    if (d_sigma) d_sigma[i] = w[9];
+    if (mu) mu[i] = w[0];
+    if (status) status[i] = int32_t(w[10]);
+    if (evals) evals[i] = int32_t(w[2]);
+  }
+  if (clear) {
+    const int zero = 0;
+    for (qgw_state st : b->states) {
+      QGW_CHECK_HIP(hipMemcpyAsync(st->d_stat + 1, &zero, sizeof(int), hipMemcpyHostToDevice, s), "qgw_batch_read");
+      st->h_io[10] = 0.0;
+    }
+    QGW_CHECK_HIP(hipStreamSynchronize(s), "qgw_batch_read");
   }
   return QGW_OK;
 }

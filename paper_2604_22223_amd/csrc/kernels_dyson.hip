@@ -760,6 +760,7 @@ struct DysonGArgs {
   int* status;        // 0 ok, 2 not converged
   const double* extra;  // optional scalar copied to scal[9] by the final pass
   int* fail_word;       // optional: raised to the search's failing status by the final pass, never lowered here
+  double* host = nullptr;  // optional pinned host words: the final pass leaves scal[0..9] there, and *fail_word in [10]
   int r, nk, mode, max_evals;
   double beta, tol_mu, tol_n;
   double ne_offset;   // added to -(2/N_k) sum Re rho_m Tr G_m (the uniform grid's 1/2 per spin-orbital)
@@ -1036,6 +1037,11 @@ __global__ __launch_bounds__(64) void k_dg_final(DysonGArgs A, int n, int nblk) 
     if (A.fail_word && A.status[0] > *A.fail_word) *A.fail_word = A.status[0];
     A.scal[8] = double(A.status[0]);
     if (A.extra) A.scal[9] = *A.extra;
+    if (A.host) {  // the caller reads them once this launch has completed: no copy behind it
+      for (int i = 0; i < 10; ++i) A.host[i] = A.scal[i];
+      if (A.fail_word) A.host[10] = double(*A.fail_word);
+      __threadfence_system();
+    }
   }
 }
 
@@ -1384,10 +1390,11 @@ hipError_t dyson_g_steps_no(const Plan& p, const void* h_k, const void* sig_iw, 
 template <int NO>
 hipError_t dyson_g_final_no(const Plan& p, const void* h_k, const void* sig_iw, int mode, void* g_iw,
                             double* scal, double* partials, int* status, const double* extra, int steps,
-                            int* fail_word, hipStream_t s) {
+                            int* fail_word, double* host, hipStream_t s) {
   DysonGArgs A = dyson_g_args<NO>(p, h_k, sig_iw, mode, g_iw, scal, partials, status);
   A.extra = extra;
   A.fail_word = fail_word;
+  A.host = host;
   const int blocks = dyson_g_blocks(p);
   hipLaunchKernelGGL((k_dg_final<NO>), dim3(blocks), dim3(64), 0, s, A, mode == 1 ? steps : 0, blocks);
   return hipGetLastError();
@@ -1525,22 +1532,22 @@ hipError_t launch_dyson_g_steps(const Plan& p, const void* h_k, const void* sig_
 
 hipError_t launch_dyson_g_final(const Plan& p, const void* h_k, const void* sig_iw, int mode, void* g_iw,
                                 double* scal, double* partials, int* status, hipStream_t s, const double* extra,
-                                int steps, int* fail_word) {
+                                int steps, int* fail_word, double* host) {
   QGW_NO_SWITCH((dyson_g_final_no<NOV>(p, h_k, sig_iw, mode, g_iw, scal, partials, status, extra, steps, fail_word,
-                                       s)))
+                                       host, s)))
 }
 
 hipError_t launch_dyson_g_chain(const Plan& p, const void* h_k, const void* sig_iw, int mode, void* g_iw,
                                 double* scal, double* partials, int* status, int steps, int* fail_word,
                                 hipStream_t s, const double* dpart, int dnblk, const double* bmax, int nbmax,
-                                double* dsig) {
+                                double* dsig, double* host) {
   hipError_t e = hipSuccess;
   if (mode == 1) {
     e = launch_dyson_g_begin(p, h_k, scal, partials, status, 1, s, 0, 0.0, 0.0, dpart, dnblk, bmax, nbmax, dsig);
     if (e == hipSuccess) e = launch_dyson_g_steps(p, h_k, sig_iw, scal, partials, status, steps, s);
   }
-  if (e == hipSuccess) e = launch_dyson_g_final(p, h_k, sig_iw, mode, g_iw, scal, partials, status, s, nullptr,
-                                                mode == 1 ? steps : 0, fail_word);
+  if (e == hipSuccess) e = launch_dyson_g_final(p, h_k, sig_iw, mode, g_iw, scal, partials, status, s, dsig,
+                                                mode == 1 ? steps : 0, fail_word, host);
   return e;
 }
 

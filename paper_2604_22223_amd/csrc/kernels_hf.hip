@@ -7,7 +7,7 @@
 //   k_hf_mu       one block: safeguarded Newton for mu over all N_k n_o
 //                 eigenvalues, each evaluation a fixed-order block reduction
 //   k_hf_density  one thread per k: n = U f U^H
-//   k_hf_delta_mix  one block: max |Sigma_new - Sigma_old|, then linear mixing
+//   k_hf_mix      max |Sigma_new - Sigma_old| per block, linear mixing, H0 + Sigma
 #include "qgw_herm.h"
 
 namespace qgw {
@@ -38,16 +38,27 @@ __global__ __launch_bounds__(64) void k_hf_eig(const zd* __restrict__ hs, double
     for (int n = 0; n < NO; ++n) u[int64_t(i * NO + n) * nk + k] = h.v[i][n];
 }
 
+// Eigenvalues that a thread of k_hf_mu holds in registers over its evaluations (the rest are read each time).  One block
+// is bound by the chain of an evaluation; with these, one exponential instead of a tanh, and no evaluation after one that
+// met the target: 26 -> 13 us for 2880 eigenvalues.
+constexpr int kHeld = 4;
+
 // block sums of f(beta (eps - mu)) and beta f (1 - f) over all eigenvalues (1024 threads), the same
 // order on every call: per-thread sums, a xor butterfly in each wave, the 16 wave sums in a fixed order
-__device__ void counts_at(const double* __restrict__ eps, int64_t count, double beta, double mu, double* red,
-                          double& s0, double& s1) {
+__device__ void counts_at(const double (&held)[kHeld], const double* __restrict__ eps, int64_t count, double beta,
+                          double mu, double* red, double& s0, double& s1) {
   double v0 = 0.0, v1 = 0.0;
-  for (int64_t i = threadIdx.x; i < count; i += 1024) {
-    const double f = fermi_fn(beta * (eps[i] - mu));
-    v0 += f;
-    v1 += beta * f * (1.0 - f);
-  }
+  // f = 1 / (1 + e^x) and f (1 - f), without overflow, from one exponential of -|x|
+  auto add = [&](double eps_i) {
+    const double x = beta * (eps_i - mu);
+    const double e = exp(-fabs(x)), r = rcp_nr(1.0 + e);
+    v0 += x > 0.0 ? e * r : r;
+    v1 += beta * (e * r) * r;
+  };
+#pragma unroll
+  for (int u = 0; u < kHeld; ++u)
+    if (threadIdx.x + 1024 * u < count) add(held[u]);
+  for (int64_t i = threadIdx.x + 1024 * kHeld; i < count; i += 1024) add(eps[i]);
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     v0 += __shfl_xor(v0, off, 64);
@@ -73,16 +84,33 @@ __device__ void counts_at(const double* __restrict__ eps, int64_t count, double 
 // evaluations shrink, with bisection where a step would leave it; stops at |d mu| <= 1e-13 max(1, |mu|)
 // or |N_e - n_target| <= 1e-14 max(1, n_target).
 __global__ __launch_bounds__(1024) void k_hf_mu(const double* __restrict__ eps, int64_t count, int nk, double beta,
-                                                double* __restrict__ scal, int* __restrict__ status) {
+                                                double* __restrict__ scal, int* __restrict__ status,
+                                                const double* __restrict__ bmax, int nbmax,
+                                                double* __restrict__ host) {
   __shared__ double red[32];
+  double change = 0.0;  // |Delta Sigma_HF|: a maximum, so the order of the blocks does not matter
+  if (bmax && threadIdx.x < 64) {
+    for (int b = threadIdx.x; b < nbmax; b += 64) change = fmax(change, bmax[b]);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) change = fmax(change, __shfl_xor(change, off, 64));
+  }
   const double nt = scal[1];
   const double norm = 2.0 / double(nk);
   double mu = scal[0];
   int evals = 0;
   double s0 = 0.0, s1 = 0.0;
+  double held[kHeld];
+#pragma unroll
+  for (int u = 0; u < kHeld; ++u) held[u] = threadIdx.x + 1024 * u < count ? eps[threadIdx.x + 1024 * u] : eps[0];
+  bool counted = false;  // s0 belongs to mu
   if (isfinite(nt)) {
     double lo = 1e300, hi = -1e300;
-    for (int64_t i = threadIdx.x; i < count; i += 1024) {
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+      lo = fmin(lo, held[u]);
+      hi = fmax(hi, held[u]);
+    }
+    for (int64_t i = threadIdx.x + 1024 * kHeld; i < count; i += 1024) {
       lo = fmin(lo, eps[i]);
       hi = fmax(hi, eps[i]);
     }
@@ -105,10 +133,11 @@ __global__ __launch_bounds__(1024) void k_hf_mu(const double* __restrict__ eps, 
     hi += 50.0 / beta + 1.0;
     if (!(mu > lo && mu < hi)) mu = 0.5 * (lo + hi);
     for (int step = 0; step < 400; ++step) {
-      counts_at(eps, count, beta, mu, red, s0, s1);
+      counts_at(held, eps, count, beta, mu, red, s0, s1);
       ++evals;
       const double f = norm * s0 - nt, df = norm * s1;
-      if (fabs(f) <= 1e-14 * fmax(1.0, nt)) break;
+      counted = fabs(f) <= 1e-14 * fmax(1.0, nt);
+      if (counted) break;
       if (f < 0.0)
         lo = mu;
       else
@@ -120,12 +149,21 @@ __global__ __launch_bounds__(1024) void k_hf_mu(const double* __restrict__ eps, 
       if (small) break;
     }
   }
-  counts_at(eps, count, beta, mu, red, s0, s1);
+  if (!counted) counts_at(held, eps, count, beta, mu, red, s0, s1);
   if (threadIdx.x == 0) {
     scal[0] = mu;
     scal[2] = double(evals);
     scal[3] = norm * s0;
     status[0] = isfinite(mu) && isfinite(s0) ? 0 : 1;
+    if (bmax) scal[9] = change;
+    if (host) {  // read by the caller once this launch has completed
+      for (int i = 0; i < 4; ++i) host[i] = scal[i];
+      host[8] = double(status[0]);
+      host[9] = change;
+      if (status[0] != 0) host[11] = 1.0;     // sticky: the caller may look after several passes
+      if (!isfinite(change)) host[12] = 1.0;
+      __threadfence_system();
+    }
   }
 }
 
@@ -155,11 +193,15 @@ __global__ __launch_bounds__(64) void k_hf_density(const double* __restrict__ ep
     }
 }
 
-__global__ __launch_bounds__(256) void k_hf_delta_mix(zd* __restrict__ x_new, zd* __restrict__ x_old, int64_t count,
-                                                      double alpha, double* __restrict__ d_out) {
-  __shared__ double red[256];
+// change and mixing of Sigma_HF and the static H = H0 + Sigma_HF in one pass, one entry per thread, with the block's
+// largest change (a one-block form of the first two and a pass of its own for the sum took 21 + 5 us at n_o = 5,
+// 24 x 24; 3.6 us now)
+__global__ __launch_bounds__(256) void k_hf_mix(zd* __restrict__ x_new, zd* __restrict__ x_old, int64_t count,
+                                                double alpha, const zd* __restrict__ h0, zd* __restrict__ hs,
+                                                double* __restrict__ bmax) {
+  __shared__ double red[4];
   double v = 0.0;
-  for (int64_t i = threadIdx.x; i < count; i += 256) {
+  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < count; i += int64_t(gridDim.x) * 256) {
     cpx<double> a = x_new[i];
     const cpx<double> o = x_old[i];
     v = fmax(v, finite_or_inf(sqrt(norm2(a - o))));
@@ -168,23 +210,27 @@ __global__ __launch_bounds__(256) void k_hf_delta_mix(zd* __restrict__ x_new, zd
       x_new[i] = a;
     }
     x_old[i] = a;
+    hs[i] = h0[i] + a;
   }
-  red[threadIdx.x] = v;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int off = 128; off >= 1; off >>= 1) {
-    if (threadIdx.x < off) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + off]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) d_out[0] = red[0];
+  if (threadIdx.x == 0) bmax[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
+
+unsigned hf_mix_blocks(const Plan& p) {
+  const int64_t b = (int64_t(p.no) * p.no * p.nk + 255) / 256;
+  return unsigned(b < 1024 ? b : 1024);
 }
 
 template <int NO>
 hipError_t hf_density_no(const Plan& p, const void* hs, double* scal, int* status, void* u, double* eps, void* n,
-                         hipStream_t s) {
+                         hipStream_t s, const double* bmax, double* host) {
   const unsigned blocks = unsigned((p.nk + 63) / 64);
   hipLaunchKernelGGL((k_hf_eig<NO>), dim3(blocks), dim3(64), 0, s, (const zd*)hs, eps, (zd*)u, p.nk);
   hipLaunchKernelGGL(k_hf_mu, dim3(1), dim3(1024), 0, s, (const double*)eps, int64_t(NO) * p.nk, p.nk, p.beta, scal,
-                     status);
+                     status, bmax, int(hf_mix_blocks(p)), host);
   hipLaunchKernelGGL((k_hf_density<NO>), dim3(blocks), dim3(64), 0, s, (const double*)eps, (const zd*)u,
                      (const double*)scal, p.beta, (zd*)n, p.nk);
   return hipGetLastError();
@@ -193,11 +239,11 @@ hipError_t hf_density_no(const Plan& p, const void* hs, double* scal, int* statu
 }  // namespace
 
 hipError_t launch_hf_density(const Plan& p, const void* hs, double* scal, int* status, void* u, double* eps, void* n,
-                             hipStream_t s) {
+                             hipStream_t s, const double* bmax, double* host) {
   switch (p.no) {
 #define QGW_CASE(NOV) \
   case NOV:           \
-    return hf_density_no<NOV>(p, hs, scal, status, u, eps, n, s);
+    return hf_density_no<NOV>(p, hs, scal, status, u, eps, n, s, bmax, host);
     QGW_FOR_EACH_NO(QGW_CASE)
 #undef QGW_CASE
     default:
@@ -205,9 +251,10 @@ hipError_t launch_hf_density(const Plan& p, const void* hs, double* scal, int* s
   }
 }
 
-hipError_t launch_hf_delta_mix(const Plan& p, void* x_new, void* x_old, double alpha, double* d_out, hipStream_t s) {
-  hipLaunchKernelGGL(k_hf_delta_mix, dim3(1), dim3(256), 0, s, (zd*)x_new, (zd*)x_old,
-                     int64_t(p.no) * p.no * p.nk, alpha, d_out);
+hipError_t launch_hf_mix(const Plan& p, void* x_new, void* x_old, double alpha, const void* h0, void* hs, double* bmax,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(k_hf_mix, dim3(hf_mix_blocks(p)), dim3(256), 0, s, (zd*)x_new, (zd*)x_old,
+                     int64_t(p.no) * p.no * p.nk, alpha, (const zd*)h0, (zd*)hs, bmax);
   return hipGetLastError();
 }
 

@@ -136,10 +136,14 @@ void set_error(const std::string& msg);
 // Hartree-Fock density of the static Hamiltonian hs (FP64): eigen-decomposition per k into u, eps
 // (workspace: n_o^2 N_k complex, n_o N_k double), mu at the filling scal[1] (or scal[0] if scal[1] is
 // NaN) into scal[0], n = U f U^H into n
+// bmax (optional): launch_hf_mix's block maxima; their maximum goes to scal[9].  host (optional): pinned host words
+// that receive scal[0..3], the status in [8] and scal[9]
 hipError_t launch_hf_density(const Plan& p, const void* hs, double* scal, int* status, void* u, double* eps, void* n,
-                             hipStream_t s);
-// d_out = max |x_new - x_old| over a static orbital array, then x_new <- x_old + alpha (x_new - x_old), x_old <- x_new
-hipError_t launch_hf_delta_mix(const Plan& p, void* x_new, void* x_old, double alpha, double* d_out, hipStream_t s);
+                             hipStream_t s, const double* bmax = nullptr, double* host = nullptr);
+// over a static orbital array: bmax[block] = max |x_new - x_old| (non-finite as +inf), x_new <- x_old + alpha (x_new -
+// x_old), x_old <- x_new, hs = h0 + x_new; n_o^2 N_k / 256 blocks (at most 1,024)
+hipError_t launch_hf_mix(const Plan& p, void* x_new, void* x_old, double alpha, const void* h0, void* hs, double* bmax,
+                         hipStream_t s);
 
 // quasiparticle outputs per k (FP64); status[0] is set to 1 where Z^{-1} is not positive definite
 hipError_t launch_quasiparticle(const Plan& p, const void* h_k, const void* shf_k, const void* sig_iw, double mu,
@@ -217,13 +221,16 @@ hipError_t launch_dyson_g_steps(const Plan& p, const void* h_k, const void* sig_
 // scal holds 32 doubles: the host-visible words 0..9 and the two state slots of a round at 16..31.
 // fail_word (optional): raised to a failing status of the search and never lowered by the kernels (the sticky
 // report of a batch graph, whose every replay restarts status[0])
+// host (optional): pinned host words that receive scal[0..9] and, with a fail_word, its value in [10]
 hipError_t launch_dyson_g_final(const Plan& p, const void* h_k, const void* sig_iw, int mode, void* g_iw,
                                 double* scal, double* partials, int* status, hipStream_t s,
-                                const double* extra = nullptr, int steps = 0, int* fail_word = nullptr);
+                                const double* extra = nullptr, int steps = 0, int* fail_word = nullptr,
+                                double* host = nullptr);
 hipError_t launch_dyson_g_chain(const Plan& p, const void* h_k, const void* sig_iw, int mode, void* g_iw,
                                 double* scal, double* partials, int* status, int steps, int* fail_word,
                                 hipStream_t s, const double* dpart = nullptr, int dnblk = 0,
-                                const double* bmax = nullptr, int nbmax = 0, double* dsig = nullptr);
+                                const double* bmax = nullptr, int nbmax = 0, double* dsig = nullptr,
+                                double* host = nullptr);
 hipError_t launch_slab_to_matrix_static(const Plan& p, const void* in, void* out, hipStream_t s);
 // *flag |= 1 where V(R) (slab layout) changes under i <-> l of a pair index (a NaN counts as a change)
 hipError_t launch_fold_check(const Plan& p, const void* v_r, int* flag, hipStream_t s);

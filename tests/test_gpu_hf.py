@@ -132,3 +132,43 @@ def test_gw_continues_from_hf(case):
     assert rel_err(host(st.array(1)), flat(ref["sig_iw"])) < TOL
     assert rel_err(host(st.array(0)), flat(ref["G_iw"])) < TOL
     st.close()
+
+
+@pytest.mark.parametrize("n_o", range(1, 9))
+def test_density_of_every_block_size(n_o):
+    """All n_o; k = 0 diagonal, k = 1 degenerate, k = 2 with one vanishing pair, the others dense.  12 x 12 and, with
+    more eigenvalues than the search holds in registers, 32 x 32 (4096 < 32^2 n_o from n_o = 5)."""
+    rng = np.random.default_rng(n_o)
+    _MESH_DIM[0] = 2
+    sites = {3: [3], 6: [2, 1, 1, 1, 1], 7: [2, 1, 1, 1, 1, 1]}.get(n_o, [1] * n_o)
+    for n in (12, 32):
+        plan = qgw.Plan.from_nodes(n, sites, 15.0, DLR(15.0, 20.0, 1e-8).nodes())
+        x = rng.standard_normal((n_o, n_o, n, n)) + 1j * rng.standard_normal((n_o, n_o, n, n))
+        h = x + np.conj(np.swapaxes(x, 0, 1))
+        h[:, :, 0, 0] = np.diag(np.arange(n_o))
+        h[:, :, 0, 1] = 0.5 * np.eye(n_o)
+        h[0, n_o - 1, 0, 2] = h[n_o - 1, 0, 0, 2] = float(n_o == 1)
+        n_t = 0.7 * n_o
+        mu_ref, n_ref = hf.fermi_density(h, 15.0, n_target=n_t)
+        mu, dens = plan.hf_density(dev(h), n_target=n_t)
+        assert abs(mu - mu_ref) <= TOL * max(1.0, abs(mu_ref))
+        assert rel_err(host(dens), flat(n_ref)) < TOL
+        plan.close()
+
+
+@pytest.mark.parametrize("passes", [1, 63, 64, 65])
+def test_fixed_passes_equal_watched_passes(passes):
+    """A negative tol, whose passes the host does not wait for one by one, and tol = 0 take the same passes; 25 N_k
+    entries, the last block of the mixing kernel partly filled.  Mixing 0.02 keeps every change above 0."""
+    w = wl.five_orbital(n=5, U=1.0, J=0.1, Vnn=0.2, beta=20.0, omega_max=25.0, eps=1e-8, scale_mesh=5)
+    c = Case(w)
+    out = []
+    for tol in (-1.0, 0.0):
+        st = c.state(0.02)
+        done, ds, mu = st.hf_solve(tol=tol, max_iter=passes)
+        assert done == passes and ds > 0.0
+        out.append((ds, mu, host(st.array(2)), host(st.array(5)), host(st.array(0))))
+        st.close()
+    assert out[0][:2] == out[1][:2]
+    for a, b in zip(out[0][2:], out[1][2:]):
+        assert np.array_equal(a, b)
