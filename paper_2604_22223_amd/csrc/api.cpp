@@ -713,12 +713,20 @@ static qgw_status run_dyson_g(const Plan& p, const void* H_k, const void* Sig_iw
   }
   // the search's first launch takes the start point as arguments and resets the status word; a fixed-mu call
   // has no search and gets mu by a copy
+  DysonGStart start;
   if (mode == 1) {
     // with the diagonal sums of H from a14 at hand and a finite start, no Gershgorin pass is needed
-    const bool use_d = dpart && std::isfinite(sc[0]);
-    QGW_CHECK_HIP(launch_dyson_g_begin(p, H_k, scal, part, stat, track, s, 1, sc[0], sc[1], use_d ? dpart : nullptr,
-                                       dnblk, bmax, nbmax, dsig_out),
-                  "qgw_dyson_G");
+    start.track = track;
+    start.set = 1;
+    start.mu0 = sc[0];
+    start.nt = sc[1];
+    if (dpart && std::isfinite(sc[0])) {
+      start.dpart = dpart;
+      start.dnblk = dnblk;
+    }
+    start.bmax = bmax;
+    start.nbmax = nbmax;
+    start.dsig = dsig_out;
   } else {
     QGW_CHECK_HIP(hipMemcpyAsync(scal, sc, 2 * sizeof(double), hipMemcpyHostToDevice, s), "qgw_dyson_G");
     QGW_CHECK_HIP(hipMemsetAsync(stat, 0, sizeof(int), s), "qgw_dyson_G");
@@ -730,10 +738,15 @@ static qgw_status run_dyson_g(const Plan& p, const void* H_k, const void* Sig_iw
   for (int round = 0;; ++round) {
     rounds = round + 1;
     // a few Newton evaluations, G at the current mu, one read-back; more rounds only if needed
-    const int steps = mode == 1 ? (round == 0 ? steps0 : 16) : 0;
-    if (mode == 1)
-      QGW_CHECK_HIP(launch_dyson_g_steps(p, H_k, Sig_iw, scal, part, stat, steps, s), "qgw_dyson_G");
-    QGW_CHECK_HIP(launch_dyson_g_final(p, H_k, Sig_iw, mode, G_iw, scal, part, stat, s, extra_src, steps, nullptr,
+    int pending = 0;
+    if (mode == 1) {
+      // where the evaluations are one launch, it may take all that the rounds together would
+      const int steps = round > 0 ? 16 : dyson_g_one_block(p) ? steps0 + (200 - steps0 + 15) / 16 * 16 : steps0;
+      QGW_CHECK_HIP(launch_dyson_g_search(p, H_k, Sig_iw, scal, part, stat, steps, round == 0 ? &start : nullptr,
+                                          &pending, s),
+                    "qgw_dyson_G");
+    }
+    QGW_CHECK_HIP(launch_dyson_g_final(p, H_k, Sig_iw, mode, G_iw, scal, part, stat, s, extra_src, pending, nullptr,
                                        h_io),
                   "qgw_dyson_G");
     if (end_ev) QGW_CHECK_HIP(hipEventRecord(end_ev, s), "qgw_dyson_G");
@@ -1857,11 +1870,15 @@ qgw_status qgw_batch_create(int32_t n, const qgw_state* states, int32_t precisio
         const Plan& p = st->plan->p;
         hipStream_t ws = b->workers[worker[i]];
         ce = enqueue_steps(st, precision == 1, false, ws, false);
+        DysonGStart start;
+        start.track = 1;
+        start.dpart = st->d_blockmax + 4096;
+        start.dnblk = start.nbmax = dyson_g_diag_blocks(p);
+        start.bmax = st->d_blockmax;
+        start.dsig = st->d_dsig;
         if (ce == hipSuccess)
           ce = launch_dyson_g_chain(p, st->Hs_k, st->Sig_iw, std::isnan(st->n_target) ? 0 : 1, st->G_iw, st->d_scal,
-                                    st->d_part, st->d_stat, mu_steps, st->d_stat + 1, ws, st->d_blockmax + 4096,
-                                    dyson_g_diag_blocks(p), st->d_blockmax, dyson_g_diag_blocks(p), st->d_dsig,
-                                    st->h_io);
+                                    st->d_part, st->d_stat, mu_steps, st->d_stat + 1, ws, start, st->h_io);
       }
     for (int w = 0; w < nw && ce == hipSuccess; ++w) {
       ce = hipEventRecord(b->events[w], b->workers[w]);

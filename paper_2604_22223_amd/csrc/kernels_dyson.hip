@@ -768,7 +768,7 @@ struct DysonGArgs {
 
 template <int NO>
 __device__ __forceinline__ void load_base(const DysonGArgs& A, int64_t gi, cpx<double> (&bm)[NO][NO]) {
-  const int m = int(gi / A.nk), k = int(gi - int64_t(m) * A.nk);
+  const int m = int(unsigned(gi) / unsigned(A.nk)), k = int(gi) - m * A.nk;  // r N_k < 2^31
   const double w = A.wn[m];
 #pragma unroll
   for (int i = 0; i < NO; ++i)
@@ -785,11 +785,29 @@ __device__ __forceinline__ void load_base(const DysonGArgs& A, int64_t gi, cpx<d
     }
 }
 
-// block-level deterministic reductions (one wavefront per block); the xor
-// butterfly leaves the same value in every lane
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
+// block-level deterministic reductions (one wavefront per block); the xor butterfly (distances 32, 16, .. 1) leaves the
+// same value in every lane.  The sum's exchanges stay in the vector unit: swaps of half and quarter waves, then
+// rotations of a row of 16 by 8 and 4 (the sums so far repeat every 16 and 8 lanes, so these are the xor partners) and
+// quad permutations.  Through LDS (__shfl_xor) its 24 dependent exchanges took longer than a 2 x 2 inverse.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  u32x2 hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  v = __hiloint2double(int(hi[0]), int(lo[0])) + __hiloint2double(int(hi[1]), int(lo[1]));
+  lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  v = __hiloint2double(int(hi[0]), int(lo[0])) + __hiloint2double(int(hi[1]), int(lo[1]));
+  v += dpp_move<0x128>(v);  // row_ror:8
+  v += dpp_move<0x124>(v);  // row_ror:4
+  v += dpp_move<0x4e>(v);   // quad_perm 2 3 0 1
+  v += dpp_move<0xb1>(v);   // quad_perm 1 0 3 2
   return v;
 }
 __device__ __forceinline__ double wave_min(double v) {
@@ -850,39 +868,48 @@ __global__ __launch_bounds__(64) void k_dg_gersh(DysonGArgs A) {
 // diag_only: partials holds only nblk diagonal sums (a14's), no Gershgorin bounds
 // bmax (optional): a14's nbmax block maxima of |Delta Sigma| (non-finite ones already +inf); their maximum goes to
 // *dsig, so that a14 needs no reduction launch of its own (the maximum is exact, so the order does not matter)
-__global__ __launch_bounds__(64) void k_dg_begin(double* __restrict__ scal, int* __restrict__ status,
-                                                 const double* __restrict__ partials, int nblk, double inv_count,
-                                                 int track, int set, double mu0, double nt, int diag_only,
-                                                 const double* __restrict__ bmax, int nbmax,
-                                                 double* __restrict__ dsig) {
-  if (bmax) {
+struct DgBegin {
+  const double* partials;
+  int nblk;
+  double inv_count;
+  int track, set;
+  double mu0, nt;
+  int diag_only;
+  const double* bmax;
+  int nbmax;
+  double* dsig;
+};
+
+// by the 64 lanes of one wavefront
+__device__ __forceinline__ void dg_begin(double* __restrict__ scal, int* __restrict__ status, const DgBegin& B) {
+  if (B.bmax) {
     double v = 0.0;
-    for (int b = threadIdx.x; b < nbmax; b += 64) v = fmax(v, bmax[b]);
+    for (int b = threadIdx.x; b < B.nbmax; b += 64) v = fmax(v, B.bmax[b]);
     v = wave_max(v);
-    if (threadIdx.x == 0) *dsig = v;
+    if (threadIdx.x == 0) *B.dsig = v;
   }
   double glo = 1e300, ghi = -1e300, dsum = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += 64) {
-    if (diag_only) {
-      dsum += partials[b];
+  for (int b = threadIdx.x; b < B.nblk; b += 64) {
+    if (B.diag_only) {
+      dsum += B.partials[b];
     } else {
-      glo = fmin(glo, partials[b]);
-      ghi = fmax(ghi, partials[nblk + b]);
-      dsum += partials[2 * nblk + b];
+      glo = fmin(glo, B.partials[b]);
+      ghi = fmax(ghi, B.partials[B.nblk + b]);
+      dsum += B.partials[2 * B.nblk + b];
     }
   }
-  if (diag_only) glo = ghi = NAN;  // no bounds: a start that is not finite stays so (status 1)
+  if (B.diag_only) glo = ghi = NAN;  // no bounds: a start that is not finite stays so (status 1)
   glo = wave_min(glo);
   ghi = wave_max(ghi);
-  const double mean = wave_sum(dsum) * inv_count;
+  const double mean = wave_sum(dsum) * B.inv_count;
   if (threadIdx.x != 0) return;
-  if (set) {
-    scal[0] = mu0;
-    scal[1] = nt;
+  if (B.set) {
+    scal[0] = B.mu0;
+    scal[1] = B.nt;
   }
   if (!isfinite(scal[0])) {
     scal[0] = 0.5 * (glo + ghi);
-  } else if (track && isfinite(scal[10]) && isfinite(mean)) {
+  } else if (B.track && isfinite(scal[10]) && isfinite(mean)) {
     scal[0] += mean - scal[10];
   }
   scal[10] = mean;
@@ -896,11 +923,16 @@ __global__ __launch_bounds__(64) void k_dg_begin(double* __restrict__ scal, int*
   status[0] = ok ? 0 : 1;
 }
 
+__global__ __launch_bounds__(64) void k_dg_begin(double* __restrict__ scal, int* __restrict__ status, DgBegin B) {
+  dg_begin(scal, status, B);
+}
+
 // The search state after j Newton steps: mu, n_target, steps taken, N_e at the last evaluation, bracket lo / hi,
 // step cap, done.  The host-visible words scal[0..7] hold it between rounds; inside a round the state after step
 // j sits in slot j % 2 (scal[16 + 8 (j % 2) ..]) and the partial sums of evaluation j in half j % 2 of the
 // partials, so that a launch reads the previous launch's slot and half while its block 0 writes the other ones.
 constexpr int kDgSlot = 16;
+constexpr int kDgMaxBlocks = 1024;  // of k_dg_eval
 
 // one Newton step of the search from the summed partials (s: sum of rho Tr G, sd: of rho Tr G^2)
 __device__ __forceinline__ void dg_newton_update(const DysonGArgs& A, double s, double sd, double (&st)[8]) {
@@ -948,7 +980,7 @@ __device__ __forceinline__ void dg_state(const DysonGArgs& A, int j, int nblk, d
   if (j >= 1 && st[7] == 0.0) {
     const double* part = A.partials + int64_t(2) * nblk * ((j - 1) & 1);
     double s = 0.0, sd = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += 64) {
+    for (int b = threadIdx.x & 63; b < nblk; b += 64) {
       s += part[b];
       sd += part[nblk + b];
     }
@@ -956,6 +988,26 @@ __device__ __forceinline__ void dg_state(const DysonGArgs& A, int j, int nblk, d
     sd = wave_sum(sd);
     dg_newton_update(A, s, sd, st);
   }
+}
+
+// one (node, k) point's share of rho Tr G and rho Tr G^2
+template <int NO>
+__device__ __forceinline__ void dg_point(const DysonGArgs& A, int64_t gi, double mu, double& acc, double& accd) {
+  cpx<double> a[NO][NO];
+  load_base<NO>(A, gi, a);
+#pragma unroll
+  for (int i = 0; i < NO; ++i) a[i][i].re += mu;
+  invert_inplace<NO>(a);
+  cpx<double> tr = mk(0.0, 0.0), tr2 = mk(0.0, 0.0);
+#pragma unroll
+  for (int i = 0; i < NO; ++i) {
+    tr = tr + a[i][i];
+#pragma unroll
+    for (int jj = 0; jj < NO; ++jj) tr2 = fma(tr2, a[i][jj], a[jj][i]);
+  }
+  const zd rh = A.rho[int(unsigned(gi) / unsigned(A.nk))];
+  acc += rh.re * tr.re - rh.im * tr.im;
+  accd += rh.re * tr2.re - rh.im * tr2.im;
 }
 
 // evaluation j of a round: N_e(mu) and dN_e/dmu at the state after j steps, as per-block partial sums
@@ -973,29 +1025,149 @@ __global__ __launch_bounds__(64) void k_dg_eval(DysonGArgs A, int j, int nblk) {
   const int64_t total = int64_t(A.r) * A.nk;
   const int64_t stride = int64_t(gridDim.x) * 64;
   double acc = 0.0, accd = 0.0;
-  for (int64_t gi = int64_t(blockIdx.x) * 64 + threadIdx.x; gi < total; gi += stride) {
-    cpx<double> a[NO][NO];
-    load_base<NO>(A, gi, a);
-#pragma unroll
-    for (int i = 0; i < NO; ++i) a[i][i].re += mu;
-    invert_inplace<NO>(a);
-    cpx<double> tr = mk(0.0, 0.0), tr2 = mk(0.0, 0.0);
-#pragma unroll
-    for (int i = 0; i < NO; ++i) {
-      tr = tr + a[i][i];
-#pragma unroll
-      for (int jj = 0; jj < NO; ++jj) tr2 = fma(tr2, a[i][jj], a[jj][i]);
-    }
-    const zd rh = A.rho[int(gi / A.nk)];
-    acc += rh.re * tr.re - rh.im * tr.im;
-    accd += rh.re * tr2.re - rh.im * tr2.im;
-  }
+  for (int64_t gi = int64_t(blockIdx.x) * 64 + threadIdx.x; gi < total; gi += stride)
+    dg_point<NO>(A, gi, mu, acc, accd);
   acc = wave_sum(acc);
   accd = wave_sum(accd);
   if (threadIdx.x == 0) {
     double* part = A.partials + int64_t(2) * nblk * (j & 1);
     part[blockIdx.x] = acc;
     part[nblk + blockIdx.x] = accd;
+  }
+}
+
+// threads of the one-block search: as many as its registers allow
+constexpr int dg_search_threads(int no) { return no <= 3 ? 1024 : no <= 5 ? 512 : 256; }
+
+// The rest of a round's evaluations in one block, which stops at convergence: with ``first`` = 0 all of them (and, with
+// ``begin``, the start before them), else those after the ``first`` that k_dg_eval launches have taken.  One compute
+// unit evaluates, so a point costs more than in k_dg_eval, but an evaluation costs no launch, also not the ones that
+// are queued beyond convergence; search_launches says where that pays.  A wavefront takes the points and the sum of one
+// of k_dg_eval's blocks at a time, so the search is the same bit for bit.  The state ends in scal[0..7].
+template <int NO>
+__global__ __launch_bounds__(dg_search_threads(NO)) void k_dg_search(DysonGArgs A, DgBegin B, int begin, int first,
+                                                                     int nblk, int steps) {
+  constexpr int W = dg_search_threads(NO) / 64;
+  __shared__ double part[2][kDgMaxBlocks];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (begin && wave == 0) dg_begin(A.scal, A.status, B);
+  __syncthreads();
+  double st[8];
+  dg_state(A, first, nblk, st);
+  const int total = A.r * A.nk;
+  for (int j = first; j < steps && st[7] == 0.0; ++j) {
+    for (int b = wave; b < nblk; b += W) {
+      double acc = 0.0, accd = 0.0;
+      for (int gi = b * 64 + lane; gi < total; gi += nblk * 64) dg_point<NO>(A, gi, st[0], acc, accd);
+      acc = wave_sum(acc);
+      accd = wave_sum(accd);
+      if (lane == 0) {
+        part[0][b] = acc;
+        part[1][b] = accd;
+      }
+    }
+    __syncthreads();
+    double s = 0.0, sd = 0.0;
+    for (int b = lane; b < nblk; b += 64) {
+      s += part[0][b];
+      sd += part[1][b];
+    }
+    s = wave_sum(s);
+    sd = wave_sum(sd);
+    __syncthreads();
+    dg_newton_update(A, s, sd, st);  // every wavefront takes the same step
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) A.scal[i] = st[i];
+  }
+}
+
+// n_o <= 2 and few points: the whole search in one block of 1024 threads, with the points' characteristic polynomials
+// in registers.  With A the matrix at the search's first mu and d = mu - that mu, det(A + d) = det A + d Tr A + d^2 and
+//   Tr G = (Tr A + 2 d) / det(A + d),  Tr G^2 = (Tr G)^2 - 2 / det(A + d)      (n_o = 1: 1 / (A + d) and its square),
+// so an evaluation reads no memory and takes one complex reciprocal a point.
+constexpr int kPolyPoints = 16;  // complex pairs (n_o = 2) or values (1) a thread holds, divided by n_o
+constexpr int kPolyNodes = 1024;
+template <int NO>
+__global__ __launch_bounds__(1024) void k_dg_search_poly(DysonGArgs A, DgBegin B, int begin, int steps) {
+  constexpr int P = kPolyPoints / NO;
+  __shared__ double red[32];
+  __shared__ zd rho[kPolyNodes + 1];  // and a zero, for the threads' slots beyond the last point
+  for (int m = threadIdx.x; m <= A.r; m += 1024) rho[m] = m < A.r ? A.rho[m] : mk(0.0, 0.0);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (begin && wave == 0) dg_begin(A.scal, A.status, B);
+  __syncthreads();
+  double st[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) st[i] = A.scal[i];
+  const int total = A.r * A.nk;
+  const double mu0 = st[0];
+  cpx<double> tr[P], det[P];
+  int node[P];
+#pragma unroll
+  for (int u = 0; u < P; ++u) {
+    const int gi = int(threadIdx.x) + 1024 * u;
+    node[u] = A.r;
+    tr[u] = mk(0.0, 0.0);
+    det[u] = mk(1.0, 1.0);  // regular at every real d
+    if (gi < total) {
+      cpx<double> a[NO][NO];
+      load_base<NO>(A, gi, a);
+      node[u] = int(unsigned(gi) / unsigned(A.nk));
+      if constexpr (NO == 1) {
+        det[u] = mk(a[0][0].re + mu0, a[0][0].im);
+      } else {
+        a[0][0].re += mu0;
+        a[1][1].re += mu0;
+        tr[u] = a[0][0] + a[1][1];
+        det[u] = fms(a[0][0] * a[1][1], a[0][1], a[1][0]);
+      }
+    }
+  }
+  for (int j = 0; j < steps && st[7] == 0.0; ++j) {
+    const double d = st[0] - mu0;
+    double acc = 0.0, accd = 0.0;
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      cpx<double> t, t2;
+      if constexpr (NO == 1) {
+        t = mk(det[u].re + d, det[u].im);
+        t = scale(conj(t), rcp_nr(norm2(t)));
+        t2 = t * t;
+      } else {
+        const cpx<double> q = mk(tr[u].re + d, tr[u].im);
+        cpx<double> di = mk(det[u].re + d * q.re, det[u].im + d * q.im);
+        di = scale(conj(di), rcp_nr(norm2(di)));
+        t = mk(q.re + d, q.im) * di;
+        t2 = t * t - scale(di, 2.0);
+      }
+      const zd rh = rho[node[u]];
+      acc += rh.re * t.re - rh.im * t.im;
+      accd += rh.re * t2.re - rh.im * t2.im;
+      if (u & 1) __builtin_amdgcn_sched_barrier(0);  // more points at once spill
+    }
+    acc = wave_sum(acc);
+    accd = wave_sum(accd);
+    if ((threadIdx.x & 63) == 0) {
+      red[wave] = acc;
+      red[16 + wave] = accd;
+    }
+    __syncthreads();
+    acc = accd = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      acc += red[w];
+      accd += red[16 + w];
+    }
+    __syncthreads();
+    dg_newton_update(A, acc, accd, st);  // every thread takes the same step
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) A.scal[i] = st[i];
   }
 }
 
@@ -1019,7 +1191,7 @@ __global__ __launch_bounds__(64) void k_dg_final(DysonGArgs A, int n, int nblk) 
 #pragma unroll
     for (int i = 0; i < NO; ++i) a[i][i].re += mu;
     invert_inplace<NO>(a);
-    const int m = int(gi / A.nk), k = int(gi - int64_t(m) * A.nk);
+    const int m = int(unsigned(gi) / unsigned(A.nk)), k = int(gi) - m * A.nk;
 #pragma unroll
     for (int i = 0; i < NO; ++i)
 #pragma unroll
@@ -1347,7 +1519,7 @@ DysonGArgs dyson_g_args(const Plan& p, const void* h_k, const void* sig_iw, int 
 // partials in each block, so that work grows with the square of the block count
 static int dyson_g_blocks(const Plan& p) {
   const int64_t need = (int64_t(p.r) * p.nk + 63) / 64;
-  const int64_t cap = p.max_blocks < 1024 ? p.max_blocks : 1024;
+  const int64_t cap = p.max_blocks < kDgMaxBlocks ? p.max_blocks : kDgMaxBlocks;
   return int(need < cap ? need : cap);
 }
 
@@ -1361,29 +1533,44 @@ int dyson_g_partials_needed(const Plan& p) {
 
 namespace {
 
-template <int NO>
-hipError_t dyson_g_begin_no(const Plan& p, const void* h_k, double* scal, double* partials, int* status, int track,
-                            int set, double mu0, double nt, const double* dpart, int dnblk, const double* bmax,
-                            int nbmax, double* dsig, hipStream_t s) {
-  if (dpart) {
-    hipLaunchKernelGGL(k_dg_begin, dim3(1), dim3(64), 0, s, scal, status, dpart, dnblk, 1.0 / (double(NO) * p.nk),
-                       track, set, mu0, nt, 1, bmax, nbmax, dsig);
-    return hipGetLastError();
-  }
-  DysonGArgs A = dyson_g_args<NO>(p, h_k, nullptr, 1, nullptr, scal, partials, status);
-  const int gb = int((p.nk + 63) / 64 < 1024 ? (p.nk + 63) / 64 : 1024);
-  hipLaunchKernelGGL((k_dg_gersh<NO>), dim3(gb), dim3(64), 0, s, A);
-  hipLaunchKernelGGL(k_dg_begin, dim3(1), dim3(64), 0, s, scal, status, (const double*)partials, gb,
-                     1.0 / (double(NO) * p.nk), track, set, mu0, nt, 0, bmax, nbmax, dsig);
-  return hipGetLastError();
+// where a search's evaluations run: the number of k_dg_eval launches, the rest in one k_dg_search.  By the work of an
+// evaluation, r N_k n_o^3.
+constexpr int64_t kSearchOneBlock = 50000, kSearchTail = 2000000;
+constexpr int kSearchLaunches = 10;
+bool search_poly(const Plan& p) { return p.no <= 2 && p.r <= kPolyNodes && int64_t(p.r) * p.nk <= 1024 * (kPolyPoints / p.no); }
+int search_launches(const Plan& p, int steps, bool tail) {
+  const int64_t work = int64_t(p.r) * p.nk * p.no * p.no * p.no;
+  if (search_poly(p) || (p.no > 2 && work <= kSearchOneBlock)) return 0;
+  return tail && work <= kSearchTail && steps > kSearchLaunches + 6 ? kSearchLaunches : steps;
 }
 
 template <int NO>
-hipError_t dyson_g_steps_no(const Plan& p, const void* h_k, const void* sig_iw, double* scal, double* partials,
-                            int* status, int steps, hipStream_t s) {
+hipError_t dyson_g_search_no(const Plan& p, const void* h_k, const void* sig_iw, double* scal, double* partials,
+                             int* status, int steps, const DysonGStart* start, int* pending, bool tail, hipStream_t s) {
   DysonGArgs A = dyson_g_args<NO>(p, h_k, sig_iw, 1, nullptr, scal, partials, status);
+  const int launches = search_launches(p, steps, tail);
+  DgBegin B = {};
+  if (start) {
+    const bool diag = start->dpart != nullptr;
+    const int gb = int((p.nk + 63) / 64 < 1024 ? (p.nk + 63) / 64 : 1024);
+    if (!diag) hipLaunchKernelGGL((k_dg_gersh<NO>), dim3(gb), dim3(64), 0, s, A);
+    B = DgBegin{diag ? start->dpart : partials, diag ? start->dnblk : gb, 1.0 / (double(NO) * p.nk), start->track,
+                start->set, start->mu0, start->nt, diag ? 1 : 0, start->bmax, start->nbmax, start->dsig};
+    if (launches > 0) hipLaunchKernelGGL(k_dg_begin, dim3(1), dim3(64), 0, s, scal, status, B);
+  }
   const int blocks = dyson_g_blocks(p);
-  for (int i = 0; i < steps; ++i) hipLaunchKernelGGL((k_dg_eval<NO>), dim3(blocks), dim3(64), 0, s, A, i, blocks);
+  for (int i = 0; i < launches; ++i) hipLaunchKernelGGL((k_dg_eval<NO>), dim3(blocks), dim3(64), 0, s, A, i, blocks);
+  if constexpr (NO <= 2) {
+    if (search_poly(p)) {
+      hipLaunchKernelGGL((k_dg_search_poly<NO>), dim3(1), dim3(1024), 0, s, A, B, start ? 1 : 0, steps);
+      *pending = 0;
+      return hipGetLastError();
+    }
+  }
+  if (launches < steps || launches == 0)
+    hipLaunchKernelGGL((k_dg_search<NO>), dim3(1), dim3(dg_search_threads(NO)), 0, s, A, B,
+                       start && launches == 0 ? 1 : 0, launches, blocks, steps);
+  *pending = launches == steps ? launches : 0;
   return hipGetLastError();
 }
 
@@ -1518,16 +1705,12 @@ hipError_t launch_dyson_w(const Plan& p, const void* v_q, const void* p_nu, void
     default: return hipErrorInvalidValue;          \
   }
 
-hipError_t launch_dyson_g_begin(const Plan& p, const void* h_k, double* scal, double* partials, int* status,
-                                int track, hipStream_t s, int set, double mu0, double nt, const double* dpart,
-                                int dnblk, const double* bmax, int nbmax, double* dsig) {
-  QGW_NO_SWITCH((dyson_g_begin_no<NOV>(p, h_k, scal, partials, status, track, set, mu0, nt, dpart, dnblk, bmax, nbmax,
-                                       dsig, s)))
-}
+bool dyson_g_one_block(const Plan& p) { return search_launches(p, 1, false) == 0; }
 
-hipError_t launch_dyson_g_steps(const Plan& p, const void* h_k, const void* sig_iw, double* scal, double* partials,
-                                int* status, int steps, hipStream_t s) {
-  QGW_NO_SWITCH((dyson_g_steps_no<NOV>(p, h_k, sig_iw, scal, partials, status, steps, s)))
+hipError_t launch_dyson_g_search(const Plan& p, const void* h_k, const void* sig_iw, double* scal, double* partials,
+                                 int* status, int steps, const DysonGStart* start, int* pending, hipStream_t s,
+                                 bool tail) {
+  QGW_NO_SWITCH((dyson_g_search_no<NOV>(p, h_k, sig_iw, scal, partials, status, steps, start, pending, tail, s)))
 }
 
 hipError_t launch_dyson_g_final(const Plan& p, const void* h_k, const void* sig_iw, int mode, void* g_iw,
@@ -1539,15 +1722,13 @@ hipError_t launch_dyson_g_final(const Plan& p, const void* h_k, const void* sig_
 
 hipError_t launch_dyson_g_chain(const Plan& p, const void* h_k, const void* sig_iw, int mode, void* g_iw,
                                 double* scal, double* partials, int* status, int steps, int* fail_word,
-                                hipStream_t s, const double* dpart, int dnblk, const double* bmax, int nbmax,
-                                double* dsig, double* host) {
+                                hipStream_t s, const DysonGStart& start, double* host) {
   hipError_t e = hipSuccess;
-  if (mode == 1) {
-    e = launch_dyson_g_begin(p, h_k, scal, partials, status, 1, s, 0, 0.0, 0.0, dpart, dnblk, bmax, nbmax, dsig);
-    if (e == hipSuccess) e = launch_dyson_g_steps(p, h_k, sig_iw, scal, partials, status, steps, s);
-  }
-  if (e == hipSuccess) e = launch_dyson_g_final(p, h_k, sig_iw, mode, g_iw, scal, partials, status, s, dsig,
-                                                mode == 1 ? steps : 0, fail_word, host);
+  int pending = 0;
+  if (mode == 1)
+    e = launch_dyson_g_search(p, h_k, sig_iw, scal, partials, status, steps, &start, &pending, s, true);
+  if (e == hipSuccess) e = launch_dyson_g_final(p, h_k, sig_iw, mode, g_iw, scal, partials, status, s, start.dsig,
+                                                pending, fail_word, host);
   return e;
 }
 

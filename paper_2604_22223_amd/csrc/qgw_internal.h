@@ -196,28 +196,37 @@ hipError_t launch_pair_sum_r(const Plan& p, const void* v_r, void* v_q0, hipStre
 // Dyson G with the chemical-potential search as a chain of launches.  Scalar
 // block scal[16] ([0] mu, [1] n_target, [2] evaluations, [3] last N_e,
 // [4-6] bracket and step cap, [7] done flag), partial sums [8 max_blocks],
-// status word.  begin: Gershgorin start if mu is not finite, resets the
-// search; steps: `steps` Newton evaluations (no-ops once done); final: G at
+// status word.  search: with a start (Gershgorin if mu is not finite) resets
+// the search; `steps` Newton evaluations (no-ops once done); final: G at
 // mu (mode 0: mu as given; mode 1: also status 2 if the search has not
-// converged).  chain = begin + steps + final (graph-capturable).
-// track = 1: a state's search, whose start moves with the mean diagonal of H since its previous search (scal[10]);
-// set = 1: scal[0..1] = (mu0, nt) first (the host's start point as kernel arguments, no copy)
-// dpart (optional): dnblk block sums of the diagonal of h_k already at hand (from a14); the Gershgorin pass is then
-// skipped, and a start that is not finite is reported as status 1 instead of replaced by the Gershgorin centre
-// bmax (optional): a14's nbmax block maxima of |Delta Sigma|, reduced into *dsig by the same launch (a14 then runs
-// without its own reduction)
-hipError_t launch_dyson_g_begin(const Plan& p, const void* h_k, double* scal, double* partials, int* status,
-                                int track, hipStream_t s, int set = 0, double mu0 = 0.0, double nt = 0.0,
-                                const double* dpart = nullptr, int dnblk = 0, const double* bmax = nullptr,
-                                int nbmax = 0, double* dsig = nullptr);
+// converged).  chain = search + final (graph-capturable).
+struct DysonGStart {
+  int track = 0;  // 1: a state's search, whose start moves with the mean diagonal of H since its previous one (scal[10])
+  int set = 0;    // 1: scal[0..1] = (mu0, nt) first (the host's start point as kernel arguments, no copy)
+  double mu0 = 0.0, nt = 0.0;
+  // optional: dnblk block sums of the diagonal of h_k already at hand (from a14); the Gershgorin pass is then skipped,
+  // and a start that is not finite is reported as status 1 instead of replaced by the Gershgorin centre
+  const double* dpart = nullptr;
+  int dnblk = 0;
+  // optional: a14's nbmax block maxima of |Delta Sigma|, reduced into *dsig by the same launch (a14 then runs without
+  // its own reduction)
+  const double* bmax = nullptr;
+  int nbmax = 0;
+  double* dsig = nullptr;
+};
+// one round; ``pending``: what launch_dyson_g_final's ``steps`` has to be.  tail: a round that may have many more
+// evaluations than it needs (a graph's fixed chain) takes the late ones in one launch.
+hipError_t launch_dyson_g_search(const Plan& p, const void* h_k, const void* sig_iw, double* scal, double* partials,
+                                 int* status, int steps, const DysonGStart* start, int* pending, hipStream_t s,
+                                 bool tail = false);
+// a round of any length is one launch that ends at convergence
+bool dyson_g_one_block(const Plan& p);
 // number of the diagonal block sums a14 leaves for the search (one per 64 static entries)
 inline int dyson_g_diag_blocks(const Plan& p) { return int((int64_t(p.no) * p.no * p.nk + 63) / 64); }
 // doubles of partial sums one chemical-potential search on plan p uses (start and evaluations)
 int dyson_g_partials_needed(const Plan& p);
-hipError_t launch_dyson_g_steps(const Plan& p, const void* h_k, const void* sig_iw, double* scal, double* partials,
-                                int* status, int steps, hipStream_t s);
 // also copies the status to scal[8] and, if extra is given, *extra to scal[9]; ``steps`` is the number of
-// evaluations launch_dyson_g_steps queued in this round (the final pass takes the step of the last one).
+// evaluations launch_dyson_g_search left pending (the final pass takes the step of the last one).
 // scal holds 32 doubles: the host-visible words 0..9 and the two state slots of a round at 16..31.
 // fail_word (optional): raised to a failing status of the search and never lowered by the kernels (the sticky
 // report of a batch graph, whose every replay restarts status[0])
@@ -228,9 +237,7 @@ hipError_t launch_dyson_g_final(const Plan& p, const void* h_k, const void* sig_
                                 double* host = nullptr);
 hipError_t launch_dyson_g_chain(const Plan& p, const void* h_k, const void* sig_iw, int mode, void* g_iw,
                                 double* scal, double* partials, int* status, int steps, int* fail_word,
-                                hipStream_t s, const double* dpart = nullptr, int dnblk = 0,
-                                const double* bmax = nullptr, int nbmax = 0, double* dsig = nullptr,
-                                double* host = nullptr);
+                                hipStream_t s, const DysonGStart& start, double* host = nullptr);
 hipError_t launch_slab_to_matrix_static(const Plan& p, const void* in, void* out, hipStream_t s);
 // *flag |= 1 where V(R) (slab layout) changes under i <-> l of a pair index (a NaN counts as a change)
 hipError_t launch_fold_check(const Plan& p, const void* v_r, int* flag, hipStream_t s);
@@ -245,7 +252,7 @@ hipError_t launch_add(const Plan& p, int64_t count, const void* a, const void* b
 // 4096 block maxima of 64 static entries (n_o^2 N_k <= 262144), and with h0, at block_scratch + 4096, the blocks'
 // sums of the diagonal of hs (dyson_g_diag_blocks of them): the mean level a state's next search starts from.
 // reduce = false leaves the block maxima unreduced (d_out untouched) for the chemical-potential search's first
-// launch to reduce (launch_dyson_g_begin with bmax).
+// launch to reduce (DysonGStart::bmax).
 hipError_t launch_delta_and_mix(const Plan& p, void* hf_new, void* c_new, void* hf_old,
                                 void* c_old, double alpha, double* d_out, double* block_scratch,
                                 hipStream_t s, const void* h0 = nullptr, void* hs = nullptr, bool reduce = true);
