@@ -55,12 +55,11 @@ __device__ __forceinline__ cpx<T> shfl_cpx(cpx<T> v, int src, int width) {
   return mk(__shfl(v.re, src, width), __shfl(v.im, src, width));
 }
 
-// ADJ: solve (I - V P)^H X = B instead, with B (pair matrix layout, dense) in place of V, and write X
-template <int NB, typename T, bool ADJ = false>
+template <int NB, typename T>
 __global__ __launch_bounds__(64) void k_dyson_w(const cpx<T>* __restrict__ vq,
                                                 const cpx<T>* __restrict__ pnu,
                                                 cpx<T>* __restrict__ wc, int64_t nmat, int nk, int64_t ld,
-                                                int* __restrict__ cond, const cpx<T>* __restrict__ rhs = nullptr) {
+                                                int* __restrict__ cond) {
   using S = DysonWShape<NB>;
   static_assert(S::SEG <= 32, "a row index must fit the five low bits of a pivot key");
   __shared__ cpx<T> sp[S::MPW * S::NN];
@@ -111,10 +110,7 @@ __global__ __launch_bounds__(64) void k_dyson_w(const cpx<T>* __restrict__ vq,
   if (valid) {
     if (half == 0) {
 #pragma unroll
-      for (int c = 0; c < NB; ++c) x[c] = ADJ ? conj(pm[c * NB + row]) : pm[row * NB + c];
-    } else if (ADJ) {
-#pragma unroll
-      for (int c = 0; c < NB; ++c) x[c] = rhs[mat * S::NN + row * NB + c];
+      for (int c = 0; c < NB; ++c) x[c] = pm[row * NB + c];
     } else {
 #pragma unroll
       for (int c = 0; c < NB; ++c) x[c] = vrow[c];
@@ -170,7 +166,7 @@ __global__ __launch_bounds__(64) void k_dyson_w(const cpx<T>* __restrict__ vq,
   if (valid && half == 1) {
     const cpx<T>* vr = vq + (int64_t(q) * NB + my_step) * NB;
 #pragma unroll
-    for (int c = 0; c < NB; ++c) sp[mw * S::NN + my_step * NB + c] = ADJ ? x[c] : x[c] - vr[c];
+    for (int c = 0; c < NB; ++c) sp[mw * S::NN + my_step * NB + c] = x[c] - vr[c];
   }
   __syncthreads();
   for (int e = lane; e < nload; e += 64) {
@@ -293,8 +289,6 @@ __device__ __forceinline__ void gj25_all(cpx<T> (&x)[3][7], cpx<T>& y, int (&cs)
   (gj25_step<T, K>(x, y, cs, kof, k24, rg, cg, xs, singular), ...);
 }
 
-// ADJ: solve (I - V P)^H X = B instead (A is formed as below, passed through the V area of LDS, which ADJ no
-// longer needs, and read back conjugate-transposed), with B (pair matrix layout, dense) in place of V; writes X
 // MVP: V P on the matrix cores (16x16x4, 2 x 2 tiles over the 25 x 25 product, 7 slices of 4 along the
 // contraction; rows, columns and slices past 25 are zero), V from LDS as the A operand and P straight from memory
 // as the B operand; I - V P then passes through the V area of LDS into the elimination layout, and the final
@@ -304,11 +298,10 @@ __device__ __forceinline__ void gj25_all(cpx<T> (&x)[3][7], cpx<T>& y, int (&cs)
 // 0.46 ms (FP64) and 0.27 ms (FP32) against 0.42 and 0.25 for the VALU product, so it is an autotuner
 // alternative and not the default.
 // one matrix; xs: a chunk of P rows, then the pivot exchange; sv: V(q)
-template <typename T, bool ADJ, bool MVP>
+template <typename T, bool MVP>
 __device__ __forceinline__ void w25_solve(const cpx<T>* __restrict__ vq, const cpx<T>* __restrict__ pnu,
                                           cpx<T>* __restrict__ wc, int64_t mat, int nk, int64_t ld,
-                                          int* __restrict__ cond, const cpx<T>* __restrict__ rhs, cpx<T>* xs,
-                                          cpx<T>* sv) {
+                                          int* __restrict__ cond, cpx<T>* xs, cpx<T>* sv) {
   constexpr int NB = W25::NB, NN = NB * NB, NS = W25::NS, NT = W25::NT, CH = W25::CH, NCH = W25::NCH;
   const int lane = threadIdx.x;
   const int rg = lane & 7, cg = lane >> 3;
@@ -381,8 +374,7 @@ __device__ __forceinline__ void w25_solve(const cpx<T>* __restrict__ vq, const c
             sv[row * NB + col] = mk(T(row == col ? 1 : 0) - cr[rt][ct][v], -ci[rt][ct][v]);
         }
     __syncthreads();
-    // A (ADJ: A^H) from LDS and the right-hand side (V, or Wbar for ADJ) from memory into the elimination layout
-    const cpx<T>* bm = ADJ ? rhs + mat * NN : vm;
+    // A from LDS and the right-hand side V from memory into the elimination layout
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int row = rg + 8 * s;
@@ -391,17 +383,17 @@ __device__ __forceinline__ void w25_solve(const cpx<T>* __restrict__ vq, const c
         const int c = cg + 8 * t;
         cpx<T> val = mk(T(0), T(0));
         if (t < 4 && c < NB)
-          val = ADJ ? conj(sv[c * NB + row]) : sv[row * NB + c];
+          val = sv[row * NB + c];
         else if (c >= NB && c < 2 * NB)
-          val = bm[row * NB + c - NB];
+          val = vm[row * NB + c - NB];
         x[s][t] = val;
       }
     }
     y = mk(T(0), T(0));
     if (c24 < NB)
-      y = ADJ ? conj(sv[c24 * NB + 24]) : sv[24 * NB + c24];
+      y = sv[24 * NB + c24];
     else if (c24 < 2 * NB)
-      y = bm[24 * NB + c24 - NB];
+      y = vm[24 * NB + c24 - NB];
   } else {
   cpx<T> pre0 = mk(T(0), T(0)), pre1 = pre0, pre2 = pre0;
   auto load_chunk = [&](int c) {
@@ -448,20 +440,6 @@ __device__ __forceinline__ void w25_solve(const cpx<T>* __restrict__ vq, const c
         }
       }
     }
-    if (ADJ) {
-      // A = I - V P through the V area (every lane has finished reading V), then back as A^H
-      __syncthreads();
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int row = rg + 8 * s, c = cg + 8 * t;
-          if (c < NB) sv[row * NB + c] = mk(T(row == c ? 1 : 0) - acc[s][t].re, -acc[s][t].im);
-        }
-      if (c24 < NB) sv[24 * NB + c24] = mk(T(c24 == 24 ? 1 : 0) - a24.re, -a24.im);
-      __syncthreads();
-    }
-    const cpx<T>* bm = ADJ ? rhs + mat * NN : nullptr;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int row = rg + 8 * s;
@@ -470,18 +448,17 @@ __device__ __forceinline__ void w25_solve(const cpx<T>* __restrict__ vq, const c
         const int c = cg + 8 * t;
         cpx<T> val = mk(T(0), T(0));
         if (t < 4 && c < NB)
-          val = ADJ ? conj(sv[c * NB + row]) : mk(T(row == c ? 1 : 0) - acc[s][t < 4 ? t : 0].re,
-                                                   -acc[s][t < 4 ? t : 0].im);
+          val = mk(T(row == c ? 1 : 0) - acc[s][t < 4 ? t : 0].re, -acc[s][t < 4 ? t : 0].im);
         else if (c >= NB && c < 2 * NB)
-          val = ADJ ? bm[row * NB + c - NB] : sv[row * NB + c - NB];
+          val = sv[row * NB + c - NB];
         x[s][t] = val;
       }
     }
     y = mk(T(0), T(0));
     if (c24 < NB)
-      y = ADJ ? conj(sv[c24 * NB + 24]) : mk(T(c24 == 24 ? 1 : 0) - a24.re, -a24.im);
+      y = mk(T(c24 == 24 ? 1 : 0) - a24.re, -a24.im);
     else if (c24 < 2 * NB)
-      y = ADJ ? bm[24 * NB + c24 - NB] : sv[24 * NB + c24 - NB];
+      y = sv[24 * NB + c24 - NB];
   }
   }
   __syncthreads();  // the last chunk has been read: its area takes the pivot exchange
@@ -495,7 +472,7 @@ __device__ __forceinline__ void w25_solve(const cpx<T>* __restrict__ vq, const c
   bool singular = false;
   gj25_all<T>(x, y, cs, kof, k24, rg, cg, xs, singular, std::make_integer_sequence<int, NB>{});
   if (singular && lane == 0) atomicOr(cond, kCondSingular);
-  // row r of the V part is row kof of W; W^C = W - V (ADJ: row kof of X)
+  // row r of the V part is row kof of W; W^C = W - V
   cpx<T>* wm = wc + mat * ld;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
@@ -503,22 +480,22 @@ __device__ __forceinline__ void w25_solve(const cpx<T>* __restrict__ vq, const c
 #pragma unroll
     for (int t = 3; t < NT; ++t) {
       const int col = cg + 8 * t - NB;
-      if (col >= 0 && col < NB) wm[k * NB + col] = ADJ ? x[s][t] : x[s][t] - (MVP ? vm : sv)[k * NB + col];
+      if (col >= 0 && col < NB) wm[k * NB + col] = x[s][t] - (MVP ? vm : sv)[k * NB + col];
     }
   }
-  if (c24 >= NB && c24 < 2 * NB) wm[k24 * NB + c24 - NB] = ADJ ? y : y - (MVP ? vm : sv)[k24 * NB + c24 - NB];
+  if (c24 >= NB && c24 < 2 * NB) wm[k24 * NB + c24 - NB] = y - (MVP ? vm : sv)[k24 * NB + c24 - NB];
 }
 
 // FP32 asks for five waves per SIMD: its elimination fits 96 VGPRs without spills (97 by default, four waves).
 // guarded: only the matrices that the folded solver left marked
-template <typename T, bool ADJ = false, bool MVP = false>
+template <typename T, bool MVP = false>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 1))) void k_dyson_w25(
     const cpx<T>* __restrict__ vq, const cpx<T>* __restrict__ pnu, cpx<T>* __restrict__ wc, int64_t nmat, int nk,
-    int64_t ld, int* __restrict__ cond, const cpx<T>* __restrict__ rhs = nullptr, int guarded = 0) {
+    int64_t ld, int* __restrict__ cond, int guarded = 0) {
   __shared__ cpx<T> xs[W25::XS];
   __shared__ cpx<T> sv[W25::NB * W25::NB];
   if (guarded && !is_left_mark(wc[int64_t(blockIdx.x) * ld])) return;
-  w25_solve<T, ADJ, MVP>(vq, pnu, wc, blockIdx.x, nk, ld, cond, rhs, xs, sv);
+  w25_solve<T, MVP>(vq, pnu, wc, blockIdx.x, nk, ld, cond, xs, sv);
 }
 
 // ---------------------------------------------------------------------------
@@ -528,7 +505,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 // columns past them are zero).  V(q) and P are staged in LDS; V P is formed in that layout; step K searches column
 // K by packed keys in the 8-lane group holding it, the owners of the pivot row and of column K publish them through
 // LDS, and every lane subtracts f_r * (pivot row).  Slots whose columns are all in I - V P and left of K drop out of
-// the update at compile time.  With ADJ it solves the conjugate-transposed system of the adjoint.
+// the update at compile time.
 // ---------------------------------------------------------------------------
 template <int NB>
 struct WR {
@@ -600,12 +577,10 @@ __device__ __forceinline__ void wr_all(cpx<T> (&x)[2][WR<NB>::NT], int (&cs)[2],
   (wr_step<T, NB, K>(x, cs, kof, rg, cg, xs, singular), ...);
 }
 
-// ADJ: solve (I - V P)^H X = B instead, with B (pair matrix layout, dense) in place of V, and write X; A = I - V P
-// passes through the P area of LDS and is read back conjugate-transposed
-template <typename T, int NB, bool ADJ = false>
+template <typename T, int NB>
 __global__ __launch_bounds__(64) void k_dyson_wr(const cpx<T>* __restrict__ vq, const cpx<T>* __restrict__ pnu,
                                                  cpx<T>* __restrict__ wc, int64_t nmat, int nk, int64_t ld,
-                                                 int* __restrict__ cond, const cpx<T>* __restrict__ rhs = nullptr) {
+                                                 int* __restrict__ cond) {
   using S = WR<NB>;
   constexpr int NT = S::NT, NN = S::NN, TA = S::TA;
   __shared__ cpx<T> sv[NN];  // V(q)
@@ -638,18 +613,6 @@ __global__ __launch_bounds__(64) void k_dyson_wr(const cpx<T>* __restrict__ vq, 
       acc[1][t] = fma(acc[1][t], v1, pj);
     }
   }
-  if constexpr (ADJ) {
-    __syncthreads();  // every lane has read P: its area takes A = I - V P
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int t = 0; t < TA; ++t) {
-        const int row = rg + 8 * s, c = cg + 8 * t;
-        if (row < NB && c < NB) sp[row * NB + c] = mk(T(row == c ? 1 : 0) - acc[s][t].re, -acc[s][t].im);
-      }
-    __syncthreads();
-  }
-  const cpx<T>* bm = ADJ ? rhs + mat * NN : nullptr;
   cpx<T> x[2][NT];
   int cs[2], kof[2];
 #pragma unroll
@@ -661,20 +624,19 @@ __global__ __launch_bounds__(64) void k_dyson_wr(const cpx<T>* __restrict__ vq, 
       const int c = cg + 8 * t;
       cpx<T> val = mk(T(0), T(0));
       if (rv && c < NB)
-        val = ADJ ? conj(sp[c * NB + row])
-                  : mk(T(row == c ? 1 : 0) - acc[s][t < TA ? t : 0].re, -acc[s][t < TA ? t : 0].im);
+        val = mk(T(row == c ? 1 : 0) - acc[s][t < TA ? t : 0].re, -acc[s][t < TA ? t : 0].im);
       else if (rv && c < 2 * NB)
-        val = ADJ ? bm[row * NB + c - NB] : sv[row * NB + c - NB];
+        val = sv[row * NB + c - NB];
       x[s][t] = val;
     }
     cs[s] = rv ? 31 - row : int(0x80000000u);  // rows past N_b never pivot
     kof[s] = 0;
   }
-  __syncthreads();  // every lane has read P (ADJ: A): its area takes the pivot exchange
+  __syncthreads();  // every lane has read P: its area takes the pivot exchange
   bool singular = false;
   wr_all<T, NB>(x, cs, kof, rg, cg, sp, singular, std::make_integer_sequence<int, NB>{});
   if (singular && lane == 0) atomicOr(cond, kCondSingular);
-  // row r of the right-hand side is row kof of the solution; W^C = W - V (ADJ: X)
+  // row r of the right-hand side is row kof of the solution; W^C = W - V
   cpx<T>* wm = wc + mat * ld;
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
@@ -683,7 +645,7 @@ __global__ __launch_bounds__(64) void k_dyson_wr(const cpx<T>* __restrict__ vq, 
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const int col = cg + 8 * t - NB;
-        if (col >= 0 && col < NB) wm[k * NB + col] = ADJ ? x[s][t] : x[s][t] - sv[k * NB + col];
+        if (col >= 0 && col < NB) wm[k * NB + col] = x[s][t] - sv[k * NB + col];
       }
     }
   }
@@ -1218,101 +1180,157 @@ __global__ __launch_bounds__(64) void k_dg_final(DysonGArgs A, int n, int nblk) 
 }
 
 // ---------------------------------------------------------------------------
-// adjoint of Dyson W (FP64).  With A = I - V P and W = A^{-1} V,
+// adjoint of Dyson W (FP64).  With A = I - V P and W = A^{-1} V, A^{-1} = I + W P and
 // dW = A^{-1} dV (I + P W) + W dP W.  For a cotangent Wbar of W^C = W - V:
-//   X = A^{-H} Wbar,  Y = X W^H,  Pbar = W^H Wbar W^H = V^H Y,
-//   Vbar = A^{-H} Wbar (I + P W)^H - Wbar = X + Y P^H - Wbar.
-// W^C and X come from the register Gauss-Jordan kernels above (the forward
-// solve, and its ADJ form on A^H with Wbar as the right-hand side); this
-// kernel forms the products.  Block (q, chunk of nodes), 256 threads: thread
-// (i, g) owns row i and the columns g, g + G, g + 2G of every product, so
-// each LDS value it loads serves three multiply-adds.  V(q) is static, so
-// Vbar(q) sums over the nodes: each block sums its chunk in a fixed order and
-// writes a partial.
+//   U = W^H Wbar,  Pbar = U W^H,  Y = Wbar W^H + P^H Pbar,
+//   Vbar = A^{-H} Wbar (I + P W)^H - Wbar = P^H U + Y P^H,
+// six products and no system to solve: W comes from the forward solve, through the folded basis where V allows it.
+// (Solving A^H X = Wbar instead took two eliminations and a pass of X through memory.)  A small block per (q, chunk of
+// nodes), so that few waves wait for each other; a lane owns a tile of R x C entries of every product, and two products
+// that are ready together share a loop.  Each step loads R + C values from LDS for R C multiply-adds, and those loads
+// bound the kernel: at 25 x 25 the 2 x 3 tiles fill 117 lanes; 4 x 3 ones in a single wavefront load less, but LDS then
+// holds one wavefront per SIMD and its latency shows.  The FP64 matrix rate equals the vector rate, so padding 25 to 32
+// on the matrix cores would only add work.  The whole adjoint, 39 nodes, V without the symmetry, before and now:
+// N_b = 25 at 32 x 32 1960 -> 1700 us; at 24 x 24 N_b = 16 502 -> 411, 9 172 -> 95, 8 135 -> 71, 4 52 -> 32, 2 33 -> 20.
+// V(q) is static, so Vbar(q) sums over the nodes: each block sums its chunk in a fixed order and writes a partial.
 // ---------------------------------------------------------------------------
 template <int NB>
-__global__ __launch_bounds__(256) void k_dyson_w_bwd_prod(const zd* __restrict__ vq, const zd* __restrict__ pnu,
-                                                          const zd* __restrict__ wbar, const zd* __restrict__ wcm,
-                                                          const zd* __restrict__ xm, zd* __restrict__ pbar,
-                                                          zd* __restrict__ vpart, int r, int nk, int chunks) {
-  constexpr int NN = NB * NB;
-  constexpr int CPT = 3;                        // columns per thread
-  constexpr int G = (NB + CPT - 1) / CPT;       // column groups
-  static_assert(NB * G <= 256, "one thread per (row, column group)");
-  __shared__ cpx<double> sV[NN], sP[NN], sX[NN], sW[NN], sY[NN];
-  const int q = blockIdx.x, ch = blockIdx.y, tid = threadIdx.x;
+struct BwdTile {
+  static constexpr int TH = NB > 16 ? 128 : 64;
+  static constexpr int R = NB > 9 ? 2 : 1, C = NB > 16 ? 3 : NB > 8 ? 2 : 1;
+  static constexpr int RG = (NB + R - 1) / R, CG = (NB + C - 1) / C;
+  static_assert(RG * CG <= TH, "one lane per tile");
+};
+
+template <int NB>
+__global__ __launch_bounds__(BwdTile<NB>::TH) void k_dyson_w_bwd(const zd* __restrict__ vq, const zd* __restrict__ pnu,
+                                                    const zd* __restrict__ wbar, const zd* __restrict__ wcm,
+                                                    zd* __restrict__ pbar, zd* __restrict__ vpart, int r, int nk,
+                                                    int chunks) {
+  using S = BwdTile<NB>;
+  constexpr int NN = NB * NB, R = S::R, C = S::C;
+  __shared__ cpx<double> sP[NN], sW[NN], sB[NN], sU[NN];  // sB: Wbar, then Pbar; sU: U, then Y
+  const int q = blockIdx.x, ch = blockIdx.y, lane = threadIdx.x;
   const int m0 = int(int64_t(r) * ch / chunks), m1 = int(int64_t(r) * (ch + 1) / chunks);
-  const bool own = tid < NB * G;
-  const int i = own ? tid / G : 0, g = tid - (tid / G) * G;
-  for (int e = tid; e < NN; e += 256) sV[e] = vq[int64_t(q) * NN + e];
-  cpx<double> vacc[CPT];
+  // rows ti + RG a and columns tj + CG b: neighbouring lanes read neighbouring values; past N_b the last one, not kept
+  const int ti = lane % S::RG, tj = min(lane / S::RG, S::CG - 1);
+  int row[R], col[C];
+  bool keep[R][C];
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) vacc[c] = mk(0.0, 0.0);
+  for (int a = 0; a < R; ++a) row[a] = min(ti + S::RG * a, NB - 1);
+#pragma unroll
+  for (int b = 0; b < C; ++b) col[b] = min(tj + S::CG * b, NB - 1);
+#pragma unroll
+  for (int a = 0; a < R; ++a)
+#pragma unroll
+    for (int b = 0; b < C; ++b)
+      keep[a][b] = lane < S::RG * S::CG && ti + S::RG * a < NB && tj + S::CG * b < NB;
+  cpx<double> vacc[R][C];
+#pragma unroll
+  for (int a = 0; a < R; ++a)
+#pragma unroll
+    for (int b = 0; b < C; ++b) vacc[a][b] = mk(0.0, 0.0);
   for (int m = m0; m < m1; ++m) {
     const int64_t base = (int64_t(m) * nk + q) * NN;
     __syncthreads();  // the previous node's products are done with the LDS tiles
-    for (int e = tid; e < NN; e += 256) {
+    for (int e = lane; e < NN; e += S::TH) {
       sP[e] = pnu[base + e];
-      sX[e] = xm[base + e];
-      sW[e] = wcm[base + e] + sV[e];  // W = W^C + V
+      sB[e] = wbar[base + e];
+      sW[e] = wcm[base + e] + vq[int64_t(q) * NN + e];  // W = W^C + V
     }
     __syncthreads();
-    // Y = X W^H
-    if (own) {
-      cpx<double> y[CPT];
+    cpx<double> u[R][C], z[R][C];
 #pragma unroll
-      for (int c = 0; c < CPT; ++c) y[c] = mk(0.0, 0.0);
-      // one k per step: an unrolled loop hoists the operand loads and runs out of registers
-#pragma unroll 1
-      for (int k = 0; k < NB; ++k) {
-        const cpx<double> a = sX[i * NB + k];
+    for (int a = 0; a < R; ++a)
 #pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-          const int j = g + c * G;
-          if (j < NB) y[c] = fma(y[c], a, conj(sW[j * NB + k]));
+      for (int b = 0; b < C; ++b) u[a][b] = z[a][b] = mk(0.0, 0.0);
+    // U = W^H Wbar,  Z = Wbar W^H
+#pragma unroll 5
+    for (int k = 0; k < NB; ++k) {
+      cpx<double> wr[R], bc[C], br[R], wc[C];
+#pragma unroll
+      for (int a = 0; a < R; ++a) wr[a] = conj(sW[k * NB + row[a]]), br[a] = sB[row[a] * NB + k];
+#pragma unroll
+      for (int b = 0; b < C; ++b) bc[b] = sB[k * NB + col[b]], wc[b] = conj(sW[col[b] * NB + k]);
+#pragma unroll
+      for (int a = 0; a < R; ++a)
+#pragma unroll
+        for (int b = 0; b < C; ++b) {
+          u[a][b] = fma(u[a][b], wr[a], bc[b]);
+          z[a][b] = fma(z[a][b], br[a], wc[b]);
         }
-      }
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        const int j = g + c * G;
-        if (j < NB) sY[i * NB + j] = y[c];
-      }
     }
+#pragma unroll
+    for (int a = 0; a < R; ++a)
+#pragma unroll
+      for (int b = 0; b < C; ++b) {
+        if (keep[a][b]) sU[row[a] * NB + col[b]] = u[a][b];
+        u[a][b] = mk(0.0, 0.0);
+      }
     __syncthreads();
-    // Pbar = V^H Y;  Vbar += X + Y P^H - Wbar
-    if (own) {
-      cpx<double> pb[CPT], vy[CPT];
+    // Pbar = U W^H,  Vbar += P^H U
+#pragma unroll 5
+    for (int k = 0; k < NB; ++k) {
+      cpx<double> ur[R], wc[C], pr[R], uc[C];
 #pragma unroll
-      for (int c = 0; c < CPT; ++c) pb[c] = vy[c] = mk(0.0, 0.0);
-#pragma unroll 1
-      for (int k = 0; k < NB; ++k) {
-        const cpx<double> vki = conj(sV[k * NB + i]), yik = sY[i * NB + k];
+      for (int a = 0; a < R; ++a) ur[a] = sU[row[a] * NB + k], pr[a] = conj(sP[k * NB + row[a]]);
 #pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-          const int j = g + c * G;
-          if (j < NB) {
-            pb[c] = fma(pb[c], vki, sY[k * NB + j]);
-            vy[c] = fma(vy[c], yik, conj(sP[j * NB + k]));
-          }
+      for (int b = 0; b < C; ++b) wc[b] = conj(sW[col[b] * NB + k]), uc[b] = sU[k * NB + col[b]];
+#pragma unroll
+      for (int a = 0; a < R; ++a)
+#pragma unroll
+        for (int b = 0; b < C; ++b) {
+          u[a][b] = fma(u[a][b], ur[a], wc[b]);
+          vacc[a][b] = fma(vacc[a][b], pr[a], uc[b]);
         }
-      }
+    }
 #pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        const int j = g + c * G;
-        if (j < NB) {
-          pbar[base + i * NB + j] = pb[c];
-          vacc[c] = vacc[c] + (sX[i * NB + j] - wbar[base + i * NB + j]) + vy[c];
+    for (int a = 0; a < R; ++a)
+#pragma unroll
+      for (int b = 0; b < C; ++b)
+        if (keep[a][b]) {
+          sB[row[a] * NB + col[b]] = u[a][b];
+          pbar[base + row[a] * NB + col[b]] = u[a][b];
         }
-      }
+    __syncthreads();
+    // Y = Z + P^H Pbar
+#pragma unroll 5
+    for (int k = 0; k < NB; ++k) {
+      cpx<double> pr[R], bc[C];
+#pragma unroll
+      for (int a = 0; a < R; ++a) pr[a] = conj(sP[k * NB + row[a]]);
+#pragma unroll
+      for (int b = 0; b < C; ++b) bc[b] = sB[k * NB + col[b]];
+#pragma unroll
+      for (int a = 0; a < R; ++a)
+#pragma unroll
+        for (int b = 0; b < C; ++b) z[a][b] = fma(z[a][b], pr[a], bc[b]);
+    }
+#pragma unroll
+    for (int a = 0; a < R; ++a)
+#pragma unroll
+      for (int b = 0; b < C; ++b)
+        if (keep[a][b]) sU[row[a] * NB + col[b]] = z[a][b];
+    __syncthreads();
+    // Vbar += Y P^H
+#pragma unroll 5
+    for (int k = 0; k < NB; ++k) {
+      cpx<double> yr[R], pc[C];
+#pragma unroll
+      for (int a = 0; a < R; ++a) yr[a] = sU[row[a] * NB + k];
+#pragma unroll
+      for (int b = 0; b < C; ++b) pc[b] = conj(sP[col[b] * NB + k]);
+#pragma unroll
+      for (int a = 0; a < R; ++a)
+#pragma unroll
+        for (int b = 0; b < C; ++b) vacc[a][b] = fma(vacc[a][b], yr[a], pc[b]);
     }
   }
-  if (own) {
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) {
-      const int j = g + c * G;
-      if (j < NB) vpart[(int64_t(ch) * nk + q) * NN + i * NB + j] = vacc[c];
-    }
-  }
+  for (int a = 0; a < R; ++a)
+#pragma unroll
+    for (int b = 0; b < C; ++b)
+      if (keep[a][b]) vpart[(int64_t(ch) * nk + q) * NN + row[a] * NB + col[b]] = vacc[a][b];
 }
 
 // ---------------------------------------------------------------------------
@@ -1415,12 +1433,12 @@ hipError_t dyson_w25(const Plan& p, const void* v_q, const void* p_nu, void* wc_
   const int64_t nmat = int64_t(p.r) * p.nk;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(unsigned(nmat)), dim3(64), 0, s, (const cpx<T>*)v_q, (const cpx<T>*)p_nu,
-                       (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord, nullptr, guarded ? 1 : 0);
+                       (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord, guarded ? 1 : 0);
   };
   if (p.tune.w25_mfma == 1)
-    go(k_dyson_w25<T, false, true>);
+    go(k_dyson_w25<T, true>);
   else
-    go(k_dyson_w25<T, false, false>);
+    go(k_dyson_w25<T, false>);
   return hipGetLastError();
 }
 
@@ -1428,7 +1446,7 @@ template <int NB, typename T>
 hipError_t dyson_wr(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, hipStream_t s, int64_t ld) {
   const int64_t nmat = int64_t(p.r) * p.nk;
   hipLaunchKernelGGL((k_dyson_wr<T, NB>), dim3(unsigned(nmat)), dim3(64), 0, s, (const cpx<T>*)v_q,
-                     (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord, nullptr);
+                     (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord);
   return hipGetLastError();
 }
 
@@ -1437,7 +1455,7 @@ hipError_t dyson_w_small(const Plan& p, const void* v_q, const void* p_nu, void*
   constexpr int MPW = DysonWShape<NB>::MPW;
   const int64_t nmat = int64_t(p.r) * p.nk;
   hipLaunchKernelGGL((k_dyson_w<NB, T>), dim3(unsigned((nmat + MPW - 1) / MPW)), dim3(64), 0, s, (const cpx<T>*)v_q,
-                     (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord, nullptr);
+                     (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, nmat, p.nk, ld, p.d_status + kCondWord);
   return hipGetLastError();
 }
 
@@ -1587,42 +1605,16 @@ hipError_t dyson_g_final_no(const Plan& p, const void* h_k, const void* sig_iw, 
   return hipGetLastError();
 }
 
-// workspace: W^C and X (pair matrix layout, dense), then the Vbar partials [chunks][N_k][N_b][N_b]
+// workspace: W^C (pair matrix layout, dense), then the Vbar partials [chunks][N_k][N_b][N_b]
 template <int NB>
 hipError_t dyson_w_bwd_nb(const Plan& p, const void* v_q, const void* p_nu, const void* wbar, void* pbar,
                           void* ws, int chunks, hipStream_t s) {
-  constexpr int64_t NN = int64_t(NB) * NB;
-  const int64_t nmat = int64_t(p.r) * p.nk;
   zd* wcm = (zd*)ws;
-  zd* xm = wcm + nmat * NN;
-  zd* vpart = xm + nmat * NN;
-  int* cond = p.d_status + kCondWord;
-  if (NB == 25 && p.tune.w25_mfma == 1) {
-    hipLaunchKernelGGL((k_dyson_w25<double, false, true>), dim3(unsigned(nmat)), dim3(64), 0, s, (const zd*)v_q,
-                       (const zd*)p_nu, wcm, nmat, p.nk, NN, cond, nullptr);
-    hipLaunchKernelGGL((k_dyson_w25<double, true, true>), dim3(unsigned(nmat)), dim3(64), 0, s, (const zd*)v_q,
-                       (const zd*)p_nu, xm, nmat, p.nk, NN, cond, (const zd*)wbar);
-  } else if (NB == 25) {
-    hipLaunchKernelGGL((k_dyson_w25<double, false, false>), dim3(unsigned(nmat)), dim3(64), 0, s, (const zd*)v_q,
-                       (const zd*)p_nu, wcm, nmat, p.nk, NN, cond, nullptr);
-    hipLaunchKernelGGL((k_dyson_w25<double, true, false>), dim3(unsigned(nmat)), dim3(64), 0, s, (const zd*)v_q,
-                       (const zd*)p_nu, xm, nmat, p.nk, NN, cond, (const zd*)wbar);
-  } else if constexpr (NB > 8 && NB <= 16) {
-    hipLaunchKernelGGL((k_dyson_wr<double, NB, false>), dim3(unsigned(nmat)), dim3(64), 0, s, (const zd*)v_q,
-                       (const zd*)p_nu, wcm, nmat, p.nk, NN, cond, nullptr);
-    hipLaunchKernelGGL((k_dyson_wr<double, NB, true>), dim3(unsigned(nmat)), dim3(64), 0, s, (const zd*)v_q,
-                       (const zd*)p_nu, xm, nmat, p.nk, NN, cond, (const zd*)wbar);
-  } else {
-    constexpr int MPW = DysonWShape<NB>::MPW;
-    const unsigned blocks = unsigned((nmat + MPW - 1) / MPW);
-    hipLaunchKernelGGL((k_dyson_w<NB, double, false>), dim3(blocks), dim3(64), 0, s, (const zd*)v_q,
-                       (const zd*)p_nu, wcm, nmat, p.nk, NN, cond, nullptr);
-    hipLaunchKernelGGL((k_dyson_w<NB, double, true>), dim3(blocks), dim3(64), 0, s, (const zd*)v_q,
-                       (const zd*)p_nu, xm, nmat, p.nk, NN, cond, (const zd*)wbar);
-  }
-  hipLaunchKernelGGL((k_dyson_w_bwd_prod<NB>), dim3(unsigned(p.nk), unsigned(chunks)), dim3(256), 0, s,
-                     (const zd*)v_q, (const zd*)p_nu, (const zd*)wbar, (const zd*)wcm, (const zd*)xm, (zd*)pbar,
-                     vpart, p.r, p.nk, chunks);
+  zd* vpart = wcm + int64_t(p.r) * p.nk * NB * NB;
+  const hipError_t e = dyson_w_t<double>(p, v_q, p_nu, wcm, s, 0, true);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_dyson_w_bwd<NB>), dim3(unsigned(p.nk), unsigned(chunks)), dim3(BwdTile<NB>::TH), 0, s, (const zd*)v_q,
+                     (const zd*)p_nu, (const zd*)wbar, (const zd*)wcm, (zd*)pbar, vpart, p.r, p.nk, chunks);
   return hipGetLastError();
 }
 

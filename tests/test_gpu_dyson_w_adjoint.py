@@ -1,0 +1,59 @@
+"""Adjoint of Dyson W at every pair-basis size, against the formula with dense solves in NumPy.
+
+W = (I - V P)^{-1} V; for a cotangent B of W - V: X = (I - V P)^{-H} B, Pbar = W^H B W^H, Vbar = sum_nodes X + X W^H P^H
+- B.  Half of the V(q) keep the pair-exchange symmetry (their W comes through the folded basis where N_b >= 9), the other
+half do not.  Entries of V P are below 0.4 / N_b, so that I - V P is well conditioned; the bar is the FP64 parity bar.
+"""
+import numpy as np
+import pytest
+
+from conftest import rel_err
+from oracle.dlr import DLR
+from paper_2604_22223_amd import qgw
+
+pytestmark = pytest.mark.gpu
+
+N, BETA = 4, 10.0
+SITES = {1: [1], 2: [1, 1], 4: [2], 5: [2, 1], 8: [2, 2], 9: [3], 16: [4], 25: [5]}
+
+
+def _exchange(sites):
+    """Index of the pair (l, i) for every pair (i, l)."""
+    out, base = [], 0
+    for n in sites:
+        out += [base + l * n + i for i in range(n) for l in range(n)]
+        base += n * n
+    return np.array(out)
+
+
+@pytest.mark.parametrize("nb", sorted(SITES))
+def test_adjoint_of_every_size(nb):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    p = qgw.Plan.from_nodes(N, SITES[nb], BETA, DLR(BETA, 10.0, 1e-8).nodes())
+    rng = np.random.default_rng(nb)
+
+    def rand(*shape):
+        return rng.uniform(-1, 1, shape) + 1j * rng.uniform(-1, 1, shape)
+
+    vq, pnu, b = rand(p.n_k, nb, nb), rand(p.r, p.n_k, nb, nb) * (0.2 / nb), rand(p.r, p.n_k, nb, nb)
+    ex = _exchange(SITES[nb])
+    for q in range(0, p.n_k, 2):
+        v = vq[q] + vq[q][ex]
+        v = v + v[:, ex]
+        vq[q] = 0.25 * v
+    a = np.eye(nb) - vq[None] @ pnu
+    w = np.linalg.solve(a, np.broadcast_to(vq[None], pnu.shape))
+    x = np.linalg.solve(np.conj(np.swapaxes(a, -1, -2)), b)
+    wh, ph = np.conj(np.swapaxes(w, -1, -2)), np.conj(np.swapaxes(pnu, -1, -2))
+    pb_ref, vb_ref = wh @ b @ wh, (x + x @ wh @ ph - b).sum(axis=0)
+
+    def dev(y):
+        return torch.from_numpy(np.ascontiguousarray(y)).to("cuda:0")
+
+    pbar, vbar = dev(np.zeros_like(pnu)), dev(np.zeros_like(vq))
+    p.dyson_W_bwd(dev(vq), dev(pnu), dev(b), pbar, vbar)
+    p.sync_status()
+    assert rel_err(pbar.cpu().numpy(), pb_ref) < 1e-10
+    assert rel_err(vbar.cpu().numpy(), vb_ref) < 1e-10
+    p.close()
