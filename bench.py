@@ -68,15 +68,22 @@ def make_workload():
     return wl.workload(WORKLOAD)
 
 
-def step_model(r, n_o, n_b, n_k, prec="f64"):
-    """Algorithmic HBM bytes and flops of each timed step.
+def pair_classes(site_norb):
+    """Unordered orbital pairs per site: the pair basis of a state whose V(R) has the pair-exchange symmetry, as the
+    benchmark's Kanamori tensors have."""
+    return sum(n * (n + 1) // 2 for n in site_norb)
+
+
+def step_model(r, n_o, n_b, n_k, prec="f64", n_p=None):
+    """Algorithmic HBM bytes and flops of each timed step (n_p: the state's pair classes, of n_b pairs).
 
     FP64 iterations hold complex128 arrays (16 bytes); the FP32 iterations run
     a1-a11 on complex64 arrays (8 bytes) and start from / end in the FP64
     G(i w) and Sigma(i w) of the solve; a12, a13 and a14 are FP64 in both."""
     c = 16.0 if prec == "f64" else 8.0
     ng = r * n_o * n_o * n_k                 # elements of one fermionic array
-    npair = r * n_b * n_b * n_k              # elements of one pair array
+    n_p = n_b if n_p is None else n_p
+    npair = r * n_p * n_p * n_k              # elements of one pair array
     stat_o = n_o * n_o * n_k * 16.0
     fft_flops = 5.0 * n_k * math.log2(max(n_k, 2))   # per slab (complex 2-D FFT)
     return {
@@ -84,11 +91,11 @@ def step_model(r, n_o, n_b, n_k, prec="f64"):
         # read G(i w) once (FP64), write G(tau) and G(beta - tau)
         "a1_dlr_g": {"bytes": 16.0 * ng + 2 * c * ng, "flops": 2 * 8.0 * r * r * n_o * n_o * n_k},
         "a2_fft_g": {"bytes": 4 * c * ng, "flops": 2 * r * n_o * n_o * fft_flops},
-        "a3a4_bubble": {"bytes": 2 * c * ng + c * npair, "flops": r * n_b * n_b * (fft_flops + 12.0 * n_k)},
-        "a5_dlr_p": {"bytes": 2 * c * npair, "flops": 8.0 * r * r * n_b * n_b * n_k},
-        "a6_dyson_w": {"bytes": 2 * c * npair + n_b * n_b * n_k * c, "flops": (8.0 + 8.0 / 3.0 + 8.0) * n_b ** 3 * r * n_k},
-        "a7_dlr_w": {"bytes": 2 * c * npair, "flops": 8.0 * r * r * n_b * n_b * n_k},
-        "a8a9a10_sigma": {"bytes": c * npair + 2 * c * ng, "flops": r * n_b * n_b * (fft_flops + 8.0 * n_k) + r * n_o * n_o * fft_flops},
+        "a3a4_bubble": {"bytes": 2 * c * ng + c * npair, "flops": r * (n_p * n_p * fft_flops + n_b * n_b * 12.0 * n_k)},
+        "a5_dlr_p": {"bytes": 2 * c * npair, "flops": 8.0 * r * r * n_p * n_p * n_k},
+        "a6_dyson_w": {"bytes": 2 * c * npair + n_p * n_p * n_k * c, "flops": (8.0 + 8.0 / 3.0 + 8.0) * n_p ** 3 * r * n_k},
+        "a7_dlr_w": {"bytes": 2 * c * npair, "flops": 8.0 * r * r * n_p * n_p * n_k},
+        "a8a9a10_sigma": {"bytes": c * npair + 2 * c * ng, "flops": r * (n_p * n_p * fft_flops + n_b * n_b * 8.0 * n_k) + r * n_o * n_o * fft_flops},
         # read Sigma^C(k, tau), write the FP64 Sigma^C(k, i w)
         "a11_dlr_sigma": {"bytes": c * ng + 16.0 * ng, "flops": 8.0 * r * r * n_o * n_o * n_k},
         # Sigma^C new and old read, old written (at mixing 1, as timed, the new values are not rewritten); Sigma_HF
@@ -106,10 +113,7 @@ PEAK_TFLOPS = {"f64": FP64_PEAK_TFLOPS, "f32": FP32_PEAK_TFLOPS}
 # profiles/hbm_traffic_gw_iteration_five_orbital_24.md).
 # Valid for the kernels as they were profiled; a changed kernel drops its entry until it is profiled again.
 MEASURED_TRAFFIC = {
-    "a3a4_bubble:f64": 332.3e6, "a5_dlr_p:f64": 671.9e6, "a6_dyson_w:f64": 629.4e6, "a7_dlr_w:f64": 655.2e6,
-    "a8a9a10_sigma:f64": 333.8e6, "a14_delta_mix:f64": 37.8e6,
-    "a3a4_bubble:f32": 166.2e6, "a5_dlr_p:f32": 334.9e6, "a6_dyson_w:f32": 314.9e6, "a7_dlr_w:f32": 309.2e6,
-    "a8a9a10_sigma:f32": 166.0e6, "a14_delta_mix:f32": 37.8e6,
+    "a14_delta_mix:f64": 37.8e6, "a14_delta_mix:f32": 37.8e6,
 }
 FP64_STEPS = ("a12_density_hf", "a14_delta_mix", "a13_dyson_g")
 
@@ -363,7 +367,7 @@ def mf_leg(torch, qgw, w, steps, tol, warmup=2, mixing=1.0, dlr_ms=None, name=""
     return res
 
 
-def adjoint_model(r, n_o, n_b, n_k):
+def adjoint_model(r, n_o, n_b, n_k, n_p=None):
     """Algorithmic HBM bytes and flops of one call of each adjoint step (FP64; S_P and S_G are one pair and one
     orbital array with nodes).  Only what the adjoint must read and write once is counted."""
     sp = 16.0 * r * n_b * n_b * n_k
@@ -376,8 +380,10 @@ def adjoint_model(r, n_o, n_b, n_k):
         "bubble_bwd": {"bytes": sp + 4 * sg, "flops": r * n_b * n_b * (fft_flops + 16.0 * n_k)},
         # W^C read, W^C-bar written, G and Sigma-bar read, G-bar written
         "sigma_bwd": {"bytes": 2 * sp + 3 * sg, "flops": 2 * r * n_b * n_b * (fft_flops + 8.0 * n_k)},
-        # P and W-bar read, P-bar written; per matrix V P, the inverse and five products of N_b^3 complex MACs
-        "dyson_W_bwd": {"bytes": 3 * sp + 2 * stat_p, "flops": 7 * 8.0 * n_b ** 3 * r * n_k},
+        # P and W-bar read, P-bar written; per matrix the forward solve over the pair classes and six products of
+        # N_b^3 complex MACs
+        "dyson_W_bwd": {"bytes": 3 * sp + 2 * stat_p,
+                        "flops": (6 * 8.0 * n_b ** 3 + (8.0 + 8.0 / 3.0 + 8.0) * (n_p or n_b) ** 3) * r * n_k},
         "dlr_transform_pairs_bwd": {"bytes": 2 * sp, "flops": 8.0 * r * r * n_b * n_b * n_k},
         "dlr_transform_bwd": {"bytes": 2 * sg, "flops": 8.0 * r * r * n_o * n_o * n_k},
         "lattice_fft_bwd": {"bytes": 2 * sg, "flops": r * n_o * n_o * fft_flops},
@@ -465,7 +471,7 @@ def adjoint_leg(torch, qgw, steps, warmup=1):
     ms = e0.elapsed_time(e1) / steps
     tot = timer.totals()
     timer.close()
-    model = adjoint_model(plan.r, plan.n_o, plan.n_b, plan.n_k)
+    model = adjoint_model(plan.r, plan.n_o, plan.n_b, plan.n_k, pair_classes(w["site_norb"]))
     calls = {}
     for n, (t, c) in tot.items():
         per = t / c
@@ -783,7 +789,7 @@ def main():
         ms_tot, iters = detail[prec]
         if iters == 0:
             continue
-        model = step_model(plan.r, plan.n_o, plan.n_b, plan.n_k, prec)
+        model = step_model(plan.r, plan.n_o, plan.n_b, plan.n_k, prec, pair_classes(w["site_norb"]))
         for name, tot in ms_tot.items():
             key = "%s:%s" % (name, prec)
             kprec = "f64" if name in FP64_STEPS else prec
@@ -815,7 +821,7 @@ def main():
 
     # the dominant kernel's roofline from the events inside the chosen schedule's timed region
     ms_tot, iters = timed["mixed"]["prof"][dom_prec]
-    model = step_model(plan.r, plan.n_o, plan.n_b, plan.n_k, dom_prec)
+    model = step_model(plan.r, plan.n_o, plan.n_b, plan.n_k, dom_prec, pair_classes(w["site_norb"]))
     kprec = "f64" if dom_step in FP64_STEPS else dom_prec
     dd = roof(model[dom_step], kprec, ms_tot[dom_step] / iters)
     log("[bench] dominant step %s: %.4f ms x %d in the timed region (%.4f ms in the breakdown pass)"
