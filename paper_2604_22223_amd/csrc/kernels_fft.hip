@@ -151,7 +151,16 @@ __global__ __launch_bounds__(256) void k_bubble(const cpx<T>* __restrict__ gt,
   for (int e = threadIdx.x; e < nloc * M::NN; e += blockDim.x) {
     const int sl2 = e / M::NN, rem = e - sl2 * M::NN;
     const int q1 = rem / N, q2 = rem - q1 * N;
-    out[(s0 + sl2) * M::NN + rem] = lds[sl2 * M::SLAB + q1 * M::LD + q2];
+    const cpx<T> v = lds[sl2 * M::SLAB + q1 * M::LD + q2];
+    cpx<T>* o = out + (s0 + sl2) * M::NN + rem;
+    // P over all pairs outgrows the caches (305 MB at 24 x 24, 25 pairs), and writing it behind the previous call's
+    // unwritten lines took 125 us against 87 into clean caches; streamed it takes 109, with the map behind it 343 -> 320
+    // us, and 43.4 -> 42.1 us for 57 MB.  Folded, it fits, and the map finds it there.  (Streaming the map's output as
+    // well lost: 320 -> 349 us.)
+    if constexpr (FOLD)
+      *o = v;
+    else
+      store_nt(o, v);
   }
 }
 

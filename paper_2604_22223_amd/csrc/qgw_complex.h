@@ -71,6 +71,13 @@ __host__ __device__ __forceinline__ cpx<T> inv(cpx<T> a) {
   return mk(a.re * d, -a.im * d);
 }
 
+// a store that the caches need not keep, for an output larger than they are
+template <typename T>
+__device__ __forceinline__ void store_nt(cpx<T>* p, cpx<T> v) {
+  __builtin_nontemporal_store(v.re, &p->re);
+  __builtin_nontemporal_store(v.im, &p->im);
+}
+
 template <typename T, typename U>
 __host__ __device__ __forceinline__ cpx<T> cast(cpx<U> a) {
   return mk(static_cast<T>(a.re), static_cast<T>(a.im));
