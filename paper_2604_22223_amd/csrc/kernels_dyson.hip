@@ -1486,7 +1486,8 @@ hipError_t dyson_w_t(const Plan& p, const void* v_q, const void* p_nu, void* wc_
     return a < b + nmat * ld * int64_t(sizeof(cpx<T>)) && b < a + count * int64_t(sizeof(cpx<T>));
   };
   bool guarded = false;
-  if (fold && !p.folded && p.fold_nb && p.nb >= 9 && nmat >= 4096 && !overlap(p_nu, nmat * nn) && !overlap(v_q, p.nk * nn)) {
+  if (fold && !p.folded && fold_solver(p.nb, p.fold_nb) && nmat >= 4096 && !overlap(p_nu, nmat * nn) &&
+      !overlap(v_q, p.nk * nn)) {
     const hipError_t e = launch_dyson_wq_fold(p, v_q, p_nu, wc_nu, ld, s);
     if (e != hipSuccess) return e;
     guarded = true;

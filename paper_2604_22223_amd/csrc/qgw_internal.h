@@ -33,8 +33,16 @@ namespace qgw {
 // Sizes whose Dyson-W solver takes four matrices per wavefront.
 #define QGW_FOR_EACH_NB_WQ(X) X(6) X(7) X(8) X(9) X(10) X(12) X(15) X(16)
 
-// Full and folded sizes (N_b >= 9) whose full matrices are solved through the folded basis.
+// Full and folded sizes (N_b >= 9) whose full matrices are solved through the folded basis; other pairs (9 and 8, of
+// sites [2, 1, 1, 1, 1, 1]) have a folded solver but not this one.
 #define QGW_FOR_EACH_FOLD(X) X(25, 15) X(25, 16) X(16, 10) X(16, 12) X(9, 6) X(9, 7)
+inline bool fold_solver(int nb, int nf) {
+#define QGW_CASE(NFV, NBV) \
+  if (nb == NFV && nf == NBV) return true;
+  QGW_FOR_EACH_FOLD(QGW_CASE)
+#undef QGW_CASE
+  return false;
+}
 
 // Orbital counts with a compiled Dyson-G solver.
 #define QGW_FOR_EACH_NO(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)

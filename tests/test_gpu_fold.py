@@ -134,3 +134,44 @@ def test_singular_system_of_a_foldable_interaction_is_reported(site_norb):
     got[3, 1] = 0.0
     assert np.all(got == 0.0)
     p.close()
+
+
+# N_b = 9 with 8 classes: a state folds it, the call on full matrices has no folded solver and takes the general one
+NINE_EIGHT = [2, 1, 1, 1, 1, 1]
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("symmetric", [True, False], ids=["folded", "full"])
+def test_state_of_nine_pairs_in_eight_classes(dim, symmetric):
+    test_state_in_the_folded_basis(NINE_EIGHT, dim, symmetric)
+
+
+@pytest.mark.parametrize("mixed", [False, True], ids=["symmetric", "some_q_not"])
+def test_dyson_w_of_nine_pairs_in_eight_classes(mixed):
+    test_dyson_w_of_a_foldable_interaction(NINE_EIGHT, 5, mixed)
+
+
+def test_adjoint_of_nine_pairs_in_eight_classes():
+    """The adjoint's forward solve at the same size (5 x 32^2 matrices), against dense solves at some q."""
+    n, rank = 32, 5
+    nodes = dict(omega=np.linspace(-1.0, 1.0, rank), tau_t=np.linspace(0.1, 0.9, rank), n_f=np.arange(rank) - 2,
+                 n_b=np.arange(rank) - 2)
+    rng = np.random.default_rng(3)
+    p = qgw.Plan.from_nodes(n, NINE_EIGHT, 3.0, nodes)
+    nb, nk = p.n_b, p.n_k
+    v = fold_v(rng, nk, NINE_EIGHT)
+    pnu, b = (rng.standard_normal((rank, nk, nb, nb)) + 1j * rng.standard_normal((rank, nk, nb, nb)) for _ in range(2))
+    pnu *= 0.05
+    pd = dev(pnu)
+    pbar, vbar = torch.zeros_like(pd), torch.zeros_like(dev(v))
+    p.dyson_W_bwd(dev(v), pd, dev(b), pbar, vbar)
+    p.sync_status()
+    some = np.array([0, 1, 31, 32, 500, nk - 1])
+    vs, ps, bs = v[some][None], pnu[:, some], b[:, some]
+    a = np.eye(nb) - vs @ ps
+    w = np.linalg.solve(a, np.broadcast_to(vs, ps.shape))
+    h = lambda x: np.conj(np.swapaxes(x, -1, -2))  # noqa: E731
+    x = np.linalg.solve(h(a), bs)
+    assert rel_err(pbar.cpu().numpy()[:, some], h(w) @ bs @ h(w)) < TOL
+    assert rel_err(vbar.cpu().numpy()[some], (x + x @ h(w) @ h(ps) - bs).sum(axis=0)) < TOL
+    p.close()
