@@ -1047,9 +1047,15 @@ __global__ __launch_bounds__(dg_search_threads(NO)) void k_dg_search(DysonGArgs 
 }
 
 // n_o <= 2 and few points: the whole search in one block of 1024 threads, with the points' characteristic polynomials
-// in registers.  With A the matrix at the search's first mu and d = mu - that mu, det(A + d) = det A + d Tr A + d^2 and
-//   Tr G = (Tr A + 2 d) / det(A + d),  Tr G^2 = (Tr G)^2 - 2 / det(A + d)      (n_o = 1: 1 / (A + d) and its square),
-// so an evaluation reads no memory and takes one complex reciprocal a point.
+// in registers.  With A the matrix at mu = c, m = Tr A / 2, s = ((A_00 - A_11) / 2)^2 + A_01 A_10 (the same at every mu),
+// q = m + (mu - c) and D = q^2 - s the determinant at mu,
+//   Tr G = 2 q / D,  Tr G^2 = (Tr G)^2 - 2 / D      (n_o = 1: 1 / q and its square),
+// so an evaluation reads no memory and takes one complex reciprocal a point.  No term grows with the distance of mu from
+// where the search began.  (An expansion of the determinant about that mu, det A + d Tr A + d^2, is 1.3 us a search faster
+// but cancels: N_e was 4e-12 off after a start 300 eV away at beta = 100/eV, past the search's tolerance of 1e-13.)
+// c = H_00 of the first point takes a common offset of the levels out of m.  N_e is then within 2e-14 of its value in
+// extended precision for beta from 10 to 500/eV, offsets up to 1000 eV and bandwidths from 0.01 to 30 eV, as it is with
+// the inverses of k_dg_eval.
 constexpr int kPolyPoints = 16;  // complex pairs (n_o = 2) or values (1) a thread holds, divided by n_o
 constexpr int kPolyNodes = 1024;
 template <int NO>
@@ -1065,45 +1071,45 @@ __global__ __launch_bounds__(1024) void k_dg_search_poly(DysonGArgs A, DgBegin B
 #pragma unroll
   for (int i = 0; i < 8; ++i) st[i] = A.scal[i];
   const int total = A.r * A.nk;
-  const double mu0 = st[0];
-  cpx<double> tr[P], det[P];
+  const double c = A.hk[0].re;
+  cpx<double> hm[P], sq[P];  // m and s
   int node[P];
 #pragma unroll
   for (int u = 0; u < P; ++u) {
     const int gi = int(threadIdx.x) + 1024 * u;
     node[u] = A.r;
-    tr[u] = mk(0.0, 0.0);
-    det[u] = mk(1.0, 1.0);  // regular at every real d
+    hm[u] = mk(0.0, 1.0);  // regular at every mu
+    sq[u] = mk(0.0, 0.0);
     if (gi < total) {
       cpx<double> a[NO][NO];
       load_base<NO>(A, gi, a);
       node[u] = int(unsigned(gi) / unsigned(A.nk));
       if constexpr (NO == 1) {
-        det[u] = mk(a[0][0].re + mu0, a[0][0].im);
+        hm[u] = mk(a[0][0].re + c, a[0][0].im);
       } else {
-        a[0][0].re += mu0;
-        a[1][1].re += mu0;
-        tr[u] = a[0][0] + a[1][1];
-        det[u] = fms(a[0][0] * a[1][1], a[0][1], a[1][0]);
+        a[0][0].re += c;
+        a[1][1].re += c;
+        hm[u] = scale(a[0][0] + a[1][1], 0.5);
+        const cpx<double> h = scale(a[0][0] - a[1][1], 0.5);
+        sq[u] = fma(h * h, a[0][1], a[1][0]);
       }
     }
   }
   for (int j = 0; j < steps && st[7] == 0.0; ++j) {
-    const double d = st[0] - mu0;
+    const double d = st[0] - c;
     double acc = 0.0, accd = 0.0;
 #pragma unroll
     for (int u = 0; u < P; ++u) {
+      const cpx<double> q = mk(hm[u].re + d, hm[u].im);
       cpx<double> t, t2;
       if constexpr (NO == 1) {
-        t = mk(det[u].re + d, det[u].im);
-        t = scale(conj(t), rcp_nr(norm2(t)));
+        t = scale(conj(q), rcp_nr(norm2(q)));
         t2 = t * t;
       } else {
-        const cpx<double> q = mk(tr[u].re + d, tr[u].im);
-        cpx<double> di = mk(det[u].re + d * q.re, det[u].im + d * q.im);
-        di = scale(conj(di), rcp_nr(norm2(di)));
-        t = mk(q.re + d, q.im) * di;
-        t2 = t * t - scale(di, 2.0);
+        cpx<double> di = q * q - sq[u];
+        di = scale(conj(di), 2.0 * rcp_nr(norm2(di)));  // 2 / D
+        t = q * di;
+        t2 = t * t - di;
       }
       const zd rh = rho[node[u]];
       acc += rh.re * t.re - rh.im * t.im;

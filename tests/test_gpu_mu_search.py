@@ -85,3 +85,44 @@ def test_late_evaluations_of_a_batch(seed):
     for st in states:
         st.close()
     plan.close()
+
+
+@pytest.mark.parametrize("sigma", [False, True])
+@pytest.mark.parametrize("n_o,n", [(1, 2), (1, 16), (2, 1), (2, 6), (3, 3)])
+def test_search_from_afar(n_o, n, sigma):
+    """Starts of tens to hundreds of eV from the solution (as far as a search from there ends at all), and levels with a
+    common offset of 1000 eV.  Where the search began must not show: it ends at a filling error of 1e-13 or a step of
+    1e-13, so the filling of the returned mu, taken from inverses in NumPy, is within 1e-13 max(1, dN/dmu) and the
+    rounding of the two evaluations, together at most twice that; at the offset the parity bar holds."""
+    torch = _torch()
+    d = DLR(100.0, 20.0, 1e-10)
+    r = len(d.iw)
+    rng = np.random.default_rng(10 * n_o + n)
+    x = rng.standard_normal((n_o, n_o, n, n)) + 1j * rng.standard_normal((n_o, n_o, n, n))
+    h = x + np.conj(np.swapaxes(x, 0, 1))
+    sig = np.zeros((r, n_o, n_o, n, n), dtype=complex)
+    if sigma:
+        c = 0.3 * (rng.standard_normal((n_o, n_o, n, n)) + 1j * rng.standard_normal((n_o, n_o, n, n)))
+        w = np.einsum("ac...,bc...->ab...", c, np.conj(c))
+        sig = np.stack([w * (0.5 / (z - 0.7) + 0.5 / (z + 0.7)) for z in d.iw])
+    nt = 0.8 * n_o
+    rho = np.asarray(d.F_iw2beta).reshape(-1)
+    base = np.moveaxis(-h[None] - sig, (1, 2), (3, 4))
+
+    def filling(mu):  # N_e and dN_e/dmu
+        g = np.linalg.inv(base + (np.asarray(d.iw)[:, None, None, None, None] + mu) * np.eye(n_o))
+        t1, t2 = np.einsum("mxyaa->m", g), np.einsum("mxyab,mxyba->m", g, g)
+        return -2.0 * (rho @ t1).real / n ** 2, 2.0 * (rho @ t2).real / n ** 2
+
+    plan = qgw.Plan.from_nodes(n, [3] if n_o == 3 else [1] * n_o, 100.0, d.nodes())
+    out = torch.empty((r, n_o, n_o, n * n), dtype=torch.complex128, device="cuda:0")
+    hd, sd = dev(h), dev(sig) if sigma else None
+    for start in (0.0, -30.0, 30.0, 100.0, -300.0):
+        mu = plan.dyson_G(hd, sd, out, n_target=nt, mu=start)
+        ne, dne = filling(mu)
+        assert abs(ne - nt) <= 2e-13 * max(1.0, dne), (start, ne - nt)
+    mu_ref, far = mu, dev(h + 1000.0 * np.eye(n_o)[:, :, None, None])
+    for start in (1000.0, 970.0, 1030.0):
+        mu = plan.dyson_G(far, sd, out, n_target=nt, mu=start)
+        assert abs(mu - 1000.0 - mu_ref) <= TOL
+    plan.close()
