@@ -563,8 +563,8 @@ qgw_status qgw_state_hf_solve(qgw_state state, double tol, int32_t max_iter,
  * i <-> l of both pair indices holds them summed and stored per unordered
  * pair: 4 is then spread over the members of each pair, and 3 is formed in
  * the full basis from that iteration's G(tau), one bubble and one map queued
- * on ``stream`` through the state's scratch.  *bytes (if not NULL) receives
- * the size. */
+ * on ``stream`` through a buffer that only these copies use.  *bytes (if not
+ * NULL) receives the size. */
 qgw_status qgw_state_copy(qgw_state state, int32_t which, void *dst, int64_t *bytes,
                           void *stream);
 

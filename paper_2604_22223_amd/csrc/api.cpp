@@ -35,10 +35,11 @@ struct qgw_state_s {
   void *G_tau = nullptr, *G_reflt = nullptr, *Sig_tau_k = nullptr;
   // V(R) has the pair-exchange symmetry: the pair arrays are kept in the folded basis of the plan copy pf.
   // G_tau_R, G_reflt_R (folded states) hold the last FP64 iteration's G(R, tau) and G(R, beta - tau), from which
-  // qgw_state_copy forms that iteration's P in the full basis
+  // qgw_state_copy forms that iteration's P in the full basis through P_full.  Iterations do not use P_full, so that a
+  // copy on another stream leaves them alone; copies that overlap write the same values there
   bool folded = false;
   Plan pf;
-  void *G_tau_R = nullptr, *G_reflt_R = nullptr;
+  void *G_tau_R = nullptr, *G_reflt_R = nullptr, *P_full = nullptr;
   // pair
   void *Pq = nullptr, *P_nu = nullptr, *Wc_nu = nullptr;
   void* hf_ws = nullptr;  // Hartree-Fock solve: eigenvectors and eigenvalues per k
@@ -1339,7 +1340,7 @@ static void free_state(qgw_state st) {
                   st->SigHF_k, st->SigHF_old, st->n_k, st->n_R, st->SigHF_R, st->Hs_k, st->G_tau,
                   st->G_reflt, st->Sig_tau_k, st->Pq, st->P_nu, st->Wc_nu, st->d_dsig, st->d_blockmax,
                   st->G32, st->Gt32, st->Gr32, st->St32, st->Siw32, st->Pq32, st->Pnu32, st->Wc32,
-                  st->Vqm32, st->d_scal, st->d_part, st->d_stat, st->hf_ws, st->G_tau_R, st->G_reflt_R};
+                  st->Vqm32, st->d_scal, st->d_part, st->d_stat, st->hf_ws, st->G_tau_R, st->G_reflt_R, st->P_full};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
 }
@@ -1410,7 +1411,7 @@ qgw_status qgw_state_create(qgw_plan h, const void* H0_R, const void* V_R, doubl
                 {&st->V_q0, size_t(p.nb) * p.nb * 16},    {&st->G_iw, fo},       {&st->Sig_iw, fo},
                 {&st->Sig_iw_old, fo}, {&st->SigHF_k, so}, {&st->SigHF_old, so},  {&st->n_k, so},
                 {&st->n_R, so},       {&st->SigHF_R, so}, {&st->Hs_k, so},       {&st->G_tau, fo},
-                {&st->G_reflt, fo},   {&st->Sig_tau_k, fo}, {&st->Pq, fp},       {&st->P_nu, fpn},
+                {&st->G_reflt, fo},   {&st->Sig_tau_k, fo}, {&st->Pq, fpn},      {&st->P_nu, fpn},
                 {&st->Wc_nu, fw},     {(void**)&st->d_dsig, 64}, {(void**)&st->d_blockmax, 8192 * sizeof(double)},
                 {(void**)&st->d_scal, 32 * sizeof(double)},
                 {(void**)&st->d_part, size_t(8) * p.max_blocks * sizeof(double)},
@@ -1423,6 +1424,7 @@ qgw_status qgw_state_create(qgw_plan h, const void* H0_R, const void* V_R, doubl
   if (st->folded) {
     if (e == hipSuccess) e = hipMalloc(&st->G_tau_R, fo);
     if (e == hipSuccess) e = hipMalloc(&st->G_reflt_R, fo);
+    if (e == hipSuccess) e = hipMalloc(&st->P_full, fp);
     if (e == hipSuccess) e = hipMemsetAsync(st->G_tau_R, 0, fo, nullptr);
     if (e == hipSuccess) e = hipMemsetAsync(st->G_reflt_R, 0, fo, nullptr);
   }
@@ -1969,10 +1971,10 @@ qgw_status qgw_state_copy(qgw_state st, int32_t which, void* dst, int64_t* bytes
   if (!dst) return QGW_OK;
   QGW_CHECK_HIP(enter_device(p.device), "hipSetDevice");
   if (st->folded && which == 3) {
-    // the bubble in the full basis from the G(tau) of the last FP64 iteration, through the state's slab buffer
+    // the bubble in the full basis from the G(tau) of the last FP64 iteration
     hipStream_t s = (hipStream_t)stream;
-    QGW_CHECK_HIP(launch_bubble(p, st->G_tau_R, st->G_reflt_R, 1, st->Pq, s), "qgw_state_copy");
-    QGW_CHECK_HIP(launch_dlr_pairs(p, QGW_B_TAU2IW, QGW_LAYOUT_SLAB, QGW_LAYOUT_MATRIX, st->Pq, dst, s),
+    QGW_CHECK_HIP(launch_bubble(p, st->G_tau_R, st->G_reflt_R, 1, st->P_full, s), "qgw_state_copy");
+    QGW_CHECK_HIP(launch_dlr_pairs(p, QGW_B_TAU2IW, QGW_LAYOUT_SLAB, QGW_LAYOUT_MATRIX, st->P_full, dst, s),
                   "qgw_state_copy");
     return QGW_OK;
   }

@@ -175,3 +175,65 @@ def test_adjoint_of_nine_pairs_in_eight_classes():
     assert rel_err(pbar.cpu().numpy()[:, some], h(w) @ bs @ h(w)) < TOL
     assert rel_err(vbar.cpu().numpy()[some], (x + x @ h(w) @ h(ps) - bs).sum(axis=0)) < TOL
     p.close()
+
+
+@pytest.mark.parametrize("dim,n,grid,eps", [(2, 5, "dlr", 1e-9), (3, 3, "dlr", 1e-9), (2, 3, "dlr", 1e-13), (2, 4, "mf", 0)])
+def test_p_of_a_folded_state_on_every_grid(dim, n, grid, eps):
+    """P of a folded state on the grids and ranks its map has (a rank above 64 among them), against the bubble and map of
+    G(i w) as the step calls make them; nothing past the end of dst."""
+    make = wl.random_model if dim == 2 else wl.random_model_3d
+    w = make((n,) * dim, [2, 1], seed=5, U=1.0, J=0.1, Vnn=0.1, beta=8.0 if eps != 1e-13 else 400.0, omega_max=16.0, eps=1e-9)
+    if grid == "mf":
+        p = qgw.Plan.uniform(n, w["site_norb"], w["beta"], 128, dim=dim)
+    else:
+        nodes = qgw.dlr_build(w["beta"] * w["omega_max"], eps)
+        nodes["omega"] = nodes["x"] / w["beta"]
+        p = qgw.Plan.from_nodes(n, w["site_norb"], w["beta"], nodes, dim=dim)
+    assert (p.r > 64) == (eps == 1e-13 or grid == "mf")
+    st = qgw.State(p, dev(flat(w["H_R"], dim)), dev(flat(w["V_R"], dim)), n_target=w["n_target"])
+    st.init_g0()
+    g0 = st.array(0)
+    st.iterate(1)
+    c = torch.complex128
+    gt, gr = (torch.empty((p.r, p.n_o, p.n_o, p.n_k), dtype=c, device="cuda:0") for _ in range(2))
+    p.dlr_transform(qgw.F_IW2TAU, g0, gt)
+    p.dlr_transform(qgw.F_IW2TAUR, g0, gr)
+    for x in (gt, gr):
+        p.lattice_fft(qgw.K_TO_R, x, x)
+    pq = torch.empty((p.r, p.n_b, p.n_b, p.n_k), dtype=c, device="cuda:0")
+    ref = torch.empty((p.r, p.n_k, p.n_b, p.n_b), dtype=c, device="cuda:0")
+    p.bubble(gt, gr, pq)
+    p.dlr_transform_pairs(qgw.B_TAU2IW, qgw.LAYOUT_SLAB, qgw.LAYOUT_MATRIX, pq, ref)
+    big = torch.full((ref.numel() + 64,), -7.0, dtype=c, device="cuda:0")
+    qgw._check(qgw.lib().qgw_state_copy(st.handle, 3, qgw._ptr(big), None, qgw._stream()))
+    assert bool((big[ref.numel():] == -7.0).all())
+    assert rel_err(big[:ref.numel()].cpu().numpy(), ref.reshape(-1).cpu().numpy()) < TOL
+    st.close()
+    p.close()
+
+
+def test_copies_of_p_do_not_disturb_iterations():
+    """Copies of P on one stream while the state iterates on another: the iterations end as without them."""
+    w = wl.five_orbital(n=12, U=1.0, J=0.1, Vnn=0.2, beta=20.0, omega_max=25.0, eps=1e-8, scale_mesh=12)
+    nodes = qgw.dlr_build(w["beta"] * w["omega_max"], w["eps"])
+    nodes["omega"] = nodes["x"] / w["beta"]
+    p = qgw.Plan.from_nodes(12, w["site_norb"], w["beta"], nodes)
+    sig = []
+    for copies in (0, 40):
+        st = qgw.State(p, dev(flat(w["H_R"], 2)), dev(flat(w["V_R"], 2)), n_target=w["n_target"])
+        st.init_g0()
+        b = qgw.Batch([st], n_iter=8)
+        other = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        b.launch()
+        with torch.cuda.stream(other):
+            for _ in range(copies):
+                st.array(3)
+        b.launch()
+        torch.cuda.synchronize()
+        assert b.read()[2][0] == 0
+        sig.append(st.array(1).cpu().numpy())
+        b.close()
+        st.close()
+    assert np.array_equal(sig[0], sig[1])
+    p.close()
