@@ -1450,6 +1450,8 @@ qgw_status qgw_state_create(qgw_plan h, const void* H0_R, const void* V_R, doubl
     for (double& v : sc) v = NAN;
     sc[1] = n_target;
     e = hipMemcpy(st->d_scal, sc, sizeof(sc), hipMemcpyHostToDevice);
+    // the same words on the host, where a batch is read: no search yet, no |Delta Sigma|, no failure
+    for (int i = 0; i < 32; ++i) st->h_io[i] = i < 10 ? sc[i] : 0.0;
   }
   if (e == hipSuccess) e = hipMemset(st->d_stat, 0, 16 * sizeof(int));
   if (e == hipSuccess) e = hipMemsetAsync(st->Sig_iw, 0, fo, s);

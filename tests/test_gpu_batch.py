@@ -280,3 +280,15 @@ def test_backward_of_every_instance_in_one_graph(insts):
             assert rel_err(H.grad.cpu().numpy(), rh) < 1e-13, (rep, k)
             assert rel_err(V.grad.cpu().numpy(), rv) < 1e-13, (rep, k)
     del g
+
+
+def test_read_before_a_launch():
+    """The words a batch is read from before any search has written them: a started state's G0 mu, and no number, no
+    failure for one that was not started."""
+    inst = Inst(SPECS[0]())
+    started, fresh = inst.state(), qgw.State(inst.plan, inst.H, inst.V, n_target=inst.w["n_target"])
+    mu0 = started.init_g0()
+    b = qgw.Batch([started, fresh])
+    ds, mu, status = b.read()
+    assert mu[0] == mu0 and np.isnan(mu[1]) and np.isnan(ds).all() and not status.any()
+    b.close()
