@@ -23,6 +23,7 @@
 // before.  Each evaluation is one launch that writes per-block partial sums;
 // a one-block launch sums them in a fixed order and takes the step, so the
 // search is deterministic and needs no grid-wide barrier.
+#include <algorithm>
 #include <cmath>
 #include <utility>
 
@@ -830,6 +831,7 @@ __global__ __launch_bounds__(64) void k_dg_gersh(DysonGArgs A) {
 // diag_only: partials holds only nblk diagonal sums (a14's), no Gershgorin bounds
 // bmax (optional): a14's nbmax block maxima of |Delta Sigma| (non-finite ones already +inf); their maximum goes to
 // *dsig, so that a14 needs no reduction launch of its own (the maximum is exact, so the order does not matter)
+constexpr int kMetWord = 2;  // of the status words: k_dg_search's count of blocks
 struct DgBegin {
   const double* partials;
   int nblk;
@@ -883,6 +885,7 @@ __device__ __forceinline__ void dg_begin(double* __restrict__ scal, int* __restr
   scal[6] = 1.0;
   scal[7] = ok ? 0.0 : 1.0;
   status[0] = ok ? 0 : 1;
+  status[kMetWord] = 0;
 }
 
 __global__ __launch_bounds__(64) void k_dg_begin(double* __restrict__ scal, int* __restrict__ status, DgBegin B) {
@@ -1001,32 +1004,82 @@ __global__ __launch_bounds__(64) void k_dg_eval(DysonGArgs A, int j, int nblk) {
 // threads of the one-block search: as many as its registers allow
 constexpr int dg_search_threads(int no) { return no <= 3 ? 1024 : no <= 5 ? 512 : 256; }
 
-// The rest of a round's evaluations in one block, which stops at convergence: with ``first`` = 0 all of them (and, with
-// ``begin``, the start before them), else those after the ``first`` that k_dg_eval launches have taken.  One compute
-// unit evaluates, so a point costs more than in k_dg_eval, but an evaluation costs no launch, also not the ones that
-// are queued beyond convergence; search_launches says where that pays.  A wavefront takes the points and the sum of one
-// of k_dg_eval's blocks at a time, so the search is the same bit for bit.  The state ends in scal[0..7].
+// The rest of a round's evaluations in one launch, which stops at convergence: with ``first`` = 0 all of them (and, with
+// ``begin``, the start before them) in one block, else those after the ``first`` that k_dg_eval launches have taken.  An
+// evaluation costs no launch, also not the ones that are queued beyond convergence; search_launches says where that
+// pays.  A wavefront takes the points and the sum of one of k_dg_eval's blocks at a time, so the search is the same bit
+// for bit.  The state ends in scal[0..7].
+// Several blocks share an evaluation's points: each adds itself to the counter status[kMetWord] (which dg_begin clears)
+// once its sums are in the partials, waits until all have, and takes the Newton step by itself.  A block writes the half
+// of evaluation j + 2 only when all blocks have added themselves for j + 1, that is, have read the half of j.  The wait
+// is bounded: a block that has looked kMeetLooks times goes on alone over all points (the same sums), adds itself no
+// more, and so sends the others alone too; every block ends whether or not the others run beside it.
+// An iteration of one three-orbital state in a batch (24 x 24, r = 52) takes 0.27 ms with 4 evaluations and 0.39 with 16,
+// in 64 launches 0.44 and 0.50; a search that uses up all 64 (n_o = 5, 12 x 12) 1.29 against 1.18.  With the late ones
+// in one block, 16 took 1.28 ms and 64 took 8.5: 33 us each at r N_k n_o^3 = 162,500 and 153 at 936,000.
+constexpr int kMeetLooks = 4096, kMeetBlocks = 64;
+
+__device__ __forceinline__ void store_agent(double* p, double v) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_agent(const double* p) {
+  return __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long*>(p),
+                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
 template <int NO>
 __global__ __launch_bounds__(dg_search_threads(NO)) void k_dg_search(DysonGArgs A, DgBegin B, int begin, int first,
                                                                      int nblk, int steps) {
   constexpr int W = dg_search_threads(NO) / 64;
   __shared__ double part[2][kDgMaxBlocks];
+  __shared__ int met;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (begin && wave == 0) dg_begin(A.scal, A.status, B);
   __syncthreads();
   double st[8];
   dg_state(A, first, nblk, st);
   const int total = A.r * A.nk;
+  bool alone = gridDim.x == 1;
   for (int j = first; j < steps && st[7] == 0.0; ++j) {
-    for (int b = wave; b < nblk; b += W) {
-      double acc = 0.0, accd = 0.0;
-      for (int gi = b * 64 + lane; gi < total; gi += nblk * 64) dg_point<NO>(A, gi, st[0], acc, accd);
-      acc = wave_sum(acc);
-      accd = wave_sum(accd);
-      if (lane == 0) {
-        part[0][b] = acc;
-        part[1][b] = accd;
+    double* const shared = A.partials + int64_t(2) * nblk * (j & 1);
+    for (;;) {
+      const int nb = alone ? 1 : int(gridDim.x);
+      for (int b = (alone ? 0 : int(blockIdx.x)) + nb * wave; b < nblk; b += nb * W) {
+        double acc = 0.0, accd = 0.0;
+        for (int gi = b * 64 + lane; gi < total; gi += nblk * 64) dg_point<NO>(A, gi, st[0], acc, accd);
+        acc = wave_sum(acc);
+        accd = wave_sum(accd);
+        if (lane == 0 && alone) {
+          part[0][b] = acc;
+          part[1][b] = accd;
+        } else if (lane == 0) {
+          store_agent(shared + b, acc);
+          store_agent(shared + nblk + b, accd);
+        }
       }
+      if (alone) break;
+      __threadfence();
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        int* const count = A.status + kMetWord;
+        const int target = (j - first + 1) * int(gridDim.x);
+        int looks = 0;
+        __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target && ++looks < kMeetLooks)
+          __builtin_amdgcn_s_sleep(2);
+        met = looks < kMeetLooks;
+        __threadfence();
+      }
+      __syncthreads();
+      if (met) {
+        for (int b = threadIdx.x; b < nblk; b += W * 64) {
+          part[0][b] = load_agent(shared + b);
+          part[1][b] = load_agent(shared + nblk + b);
+        }
+        break;
+      }
+      alone = true;
     }
     __syncthreads();
     double s = 0.0, sd = 0.0;
@@ -1040,7 +1093,7 @@ __global__ __launch_bounds__(dg_search_threads(NO)) void k_dg_search(DysonGArgs 
     dg_newton_update(A, s, sd, st);  // every wavefront takes the same step
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) A.scal[i] = st[i];
   }
@@ -1558,8 +1611,8 @@ int dyson_g_partials_needed(const Plan& p) {
 
 namespace {
 
-// where a search's evaluations run: the number of k_dg_eval launches, the rest in one k_dg_search.  By the work of an
-// evaluation, r N_k n_o^3.
+// Where a search's evaluations run: the number of k_dg_eval launches, the rest in one k_dg_search.  By the work of an
+// evaluation, r N_k n_o^3: up to 50,000 one block takes an evaluation in 10 us or less, a launch 12.
 constexpr int64_t kSearchOneBlock = 50000, kSearchTail = 2000000;
 constexpr int kSearchLaunches = 10;
 bool search_poly(const Plan& p) { return p.no <= 2 && p.r <= kPolyNodes && int64_t(p.r) * p.nk <= 1024 * (kPolyPoints / p.no); }
@@ -1592,9 +1645,11 @@ hipError_t dyson_g_search_no(const Plan& p, const void* h_k, const void* sig_iw,
       return hipGetLastError();
     }
   }
-  if (launches < steps || launches == 0)
-    hipLaunchKernelGGL((k_dg_search<NO>), dim3(1), dim3(dg_search_threads(NO)), 0, s, A, B,
+  if (launches < steps || launches == 0) {
+    const int per = dg_search_threads(NO) / 64, meet = std::min((blocks + per - 1) / per, kMeetBlocks);
+    hipLaunchKernelGGL((k_dg_search<NO>), dim3(launches == 0 ? 1 : meet), dim3(dg_search_threads(NO)), 0, s, A, B,
                        start && launches == 0 ? 1 : 0, launches, blocks, steps);
+  }
   *pending = launches == steps ? launches : 0;
   return hipGetLastError();
 }

@@ -126,3 +126,33 @@ def test_search_from_afar(n_o, n, sigma):
         mu = plan.dyson_G(far, sd, out, n_target=nt, mu=start)
         assert abs(mu - 1000.0 - mu_ref) <= TOL
     plan.close()
+
+
+@pytest.mark.parametrize("sites,n", [([2, 1], 24), ([2, 1, 1, 1, 1], 9), ([4, 3], 6), ([2, 2, 2, 2], 6)], ids=str)
+def test_late_evaluations_in_several_blocks(sites, n):
+    """As above on larger systems, whose late evaluations several blocks share, against the
+    eager search's launches: the first two iterations of almost full bands, the first with more than ten evaluations
+    except at [2, 1] (nine)."""
+    full = 2.0 * sum(sites)
+    w = wl.random_model((n, n), sites, seed=7, beta=300.0, omega_max=12.0, eps=1e-8, U=4.0, J=0.3, Vnn=0.5,
+                        n_target=full - 1e-6)
+    nodes = qgw.dlr_build(w["beta"] * w["omega_max"], w["eps"])
+    nodes["omega"] = nodes["x"] / w["beta"]
+    plan = qgw.Plan.from_nodes(n, sites, w["beta"], nodes)
+    states = [qgw.State(plan, dev(w["H_R"]), dev(w["V_R"]), n_target=w["n_target"], mixing=0.5) for _ in range(2)]
+    for st in states:
+        st.init_g0()
+    b = qgw.Batch([states[0]], mu_steps=64)
+    for it in range(2):
+        b.launch()
+        ds, mu, status, evals = b.read(with_evals=True)
+        _, ds_ref, mu_ref = states[1].iterate(1)
+        assert status[0] == 0 and evals[0] == states[1].mu_evals()
+        assert it > 0 or evals[0] > (8 if sites == [2, 1] else 10)
+        assert abs(mu[0] - mu_ref) <= TOL * abs(mu_ref)
+        assert abs(ds[0] - ds_ref) <= TOL * ds_ref
+        assert rel_err(states[0].array(0).cpu().numpy(), states[1].array(0).cpu().numpy()) < TOL
+    b.close()
+    for st in states:
+        st.close()
+    plan.close()
