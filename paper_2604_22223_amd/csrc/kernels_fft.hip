@@ -71,8 +71,9 @@ __global__ __launch_bounds__(256) void k_lattice_fft(const cpx<T>* __restrict__ 
 // FOLD: alpha and beta are classes of the folded pair basis, and the products are summed over the members (i l), (l i)
 // and (j k), (k j) of both before the transform: as many products per node as without it (they read G from L2), but
 // N_b (N_b in classes) squared transforms and stores, 225 instead of 625 for five orbitals.
+// NT: the output is streamed past the caches (bubble_n says when)
 // ---------------------------------------------------------------------------
-template <int N, bool OUTQ, typename T, bool FOLD = false>
+template <int N, bool OUTQ, typename T, bool FOLD = false, bool NT = false>
 __global__ __launch_bounds__(256) void k_bubble(const cpx<T>* __restrict__ gt,
                                                 const cpx<T>* __restrict__ gr,
                                                 cpx<T>* __restrict__ out, int64_t nslabs, int spb,
@@ -153,14 +154,10 @@ __global__ __launch_bounds__(256) void k_bubble(const cpx<T>* __restrict__ gt,
     const int q1 = rem / N, q2 = rem - q1 * N;
     const cpx<T> v = lds[sl2 * M::SLAB + q1 * M::LD + q2];
     cpx<T>* o = out + (s0 + sl2) * M::NN + rem;
-    // P over all pairs outgrows the caches (305 MB at 24 x 24, 25 pairs), and writing it behind the previous call's
-    // unwritten lines took 125 us against 87 into clean caches; streamed it takes 109, with the map behind it 343 -> 320
-    // us, and 43.4 -> 42.1 us for 57 MB.  Folded, it fits, and the map finds it there.  (Streaming the map's output as
-    // well lost: 320 -> 349 us.)
-    if constexpr (FOLD)
-      *o = v;
-    else
+    if constexpr (NT)
       store_nt(o, v);
+    else
+      *o = v;
   }
 }
 
@@ -328,6 +325,15 @@ hipError_t fft_n(const Plan& p, int dir, int64_t batch, const void* in, void* ou
   return fft_signed<N, T>(p, dir > 0 ? +1 : -1, dir > 0 ? T(1) / T(N * N) : T(1), batch, in, out, s, in2, out2);
 }
 
+// Whether the bubble over all pairs is streamed past the caches, by the bytes of its output.  From 128 MiB on P and the
+// map's output behind it outgrow the 256 MB memory-side cache, and plain stores wait for the previous lines' write-back:
+// bubble and map together 344 us plain, 322 streamed, at 305 MB (five orbitals, 24 x 24, FP64), 186 and 178 at 153 MB
+// (FP32), 145 and 144 at 136 MB.  Below that the map finds P in the cache: 97 plain, 109 streamed, at 123 MB (16 x 16),
+// 61 and 69 at 61 MB and 46 and 52 at 35 MB (FP32).  Up to 30 MB, what the eight L2 caches hold, streaming is the better
+// again: 42.0 plain, 39.1 streamed, at 27 MB (two sites, 45 x 45, FP32), the same from 10 MB down.  (Streaming the map's
+// output as well lost: 320 -> 349 us at 305 MB.)
+inline bool bubble_streams(int64_t bytes) { return bytes <= 30000000 || bytes >= (int64_t(128) << 20); }
+
 template <int N, typename T>
 hipError_t bubble_n(const Plan& p, const void* gt, const void* gr, int out_q, void* out,
                     hipStream_t s) {
@@ -345,9 +351,14 @@ hipError_t bubble_n(const Plan& p, const void* gt, const void* gr, int out_q, vo
                        p.d_pairs, twiddles<T>(p));
   } else if (out_q) {
     const size_t lds = size_t(spb) * MeshShape<N>::SLAB * sizeof(cpx<T>);
-    hipLaunchKernelGGL((k_bubble<N, true, T>), dim3(unsigned(blocks)), dim3(spb * N), lds, s,
-                       (const cpx<T>*)gt, (const cpx<T>*)gr, (cpx<T>*)out, nslabs, spb, p.no, p.nb,
-                       p.d_pairs, twiddles<T>(p));
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(unsigned(blocks)), dim3(spb * N), lds, s, (const cpx<T>*)gt, (const cpx<T>*)gr,
+                         (cpx<T>*)out, nslabs, spb, p.no, p.nb, p.d_pairs, twiddles<T>(p));
+    };
+    if (bubble_streams(nslabs * N * N * int64_t(sizeof(cpx<T>))))
+      go(k_bubble<N, true, T, false, true>);
+    else
+      go(k_bubble<N, true, T>);
   } else {
     hipLaunchKernelGGL((k_bubble<N, false, T>), dim3(unsigned(blocks)), dim3(spb * N), 0, s,
                        (const cpx<T>*)gt, (const cpx<T>*)gr, (cpx<T>*)out, nslabs, spb, p.no, p.nb,
