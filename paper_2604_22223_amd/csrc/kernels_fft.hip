@@ -8,8 +8,6 @@
 // elements so that the strided column reads of the second pass spread over
 // the banks.  One thread owns one mesh line per pass and transforms it in
 // registers (qgw_fft_reg.h).
-#include <algorithm>
-
 #include "qgw_fft_reg.h"
 #include "qgw_internal.h"
 
@@ -300,10 +298,8 @@ template <int N, typename T>
 hipError_t fft_signed(const Plan& p, int sign, T sc, int64_t batch, const void* in, void* out, hipStream_t s,
                       const void* in2 = nullptr, void* out2 = nullptr) {
   if (batch <= 0) return hipSuccess;
-  // untuned: no more slabs per block than leave two blocks per CU (of 256), but a wavefront's worth of lines: the few
-  // slabs of a static array (n_o^2 = 25 at 24 x 24) took 12 us in three blocks
-  const int64_t all = in2 ? 2 * batch : batch;
-  const int spread = int(std::min<int64_t>(std::max<int64_t>((all + 511) / 512, (64 + N - 1) / N), 256));
+  // from sides of 30 on a full block holds 5-8 slabs, and fewer gained little or lost (64 slabs of 36 x 36: 10.3 -> 10.7 us)
+  const int spread = N < 30 ? spread_slabs(in2 ? 2 * batch : batch, N) : 0;
   const int spb = tuned_spb<T>(N, p.tune.fft_spb > 0 ? p.tune.fft_spb : spread);
   const size_t lds = size_t(spb) * MeshShape<N>::SLAB * sizeof(cpx<T>);
   const int64_t blocks = (batch + spb - 1) / spb + (in2 ? (batch + spb - 1) / spb : 0);

@@ -13,8 +13,6 @@
 // through LDS, where the slab is stored with strides S2 = N + 1 (axis 2) and
 // S1 = N (N + 1) (axis 1) so that the lines of the axis-3 pass, N + 1
 // elements apart, spread over the banks.
-#include <algorithm>
-
 #include "qgw_fft_reg.h"
 #include "qgw_internal.h"
 
@@ -444,9 +442,7 @@ const cpx<float>* tw3<float>(const Plan& p) {
 template <int N, typename T>
 hipError_t fft3_n(const Plan& p, int sign, T sc, int64_t batch, const void* in, void* out, hipStream_t s) {
   if (batch <= 0) return hipSuccess;
-  // untuned: as in the 2-D form
-  const int64_t spread = std::max<int64_t>((batch + 511) / 512, (64 + Cube<N>::LINES - 1) / Cube<N>::LINES);
-  const int spb = cube_spb<N, T>(p.tune.fft_spb > 0 ? p.tune.fft_spb : int(std::min<int64_t>(spread, 256)));
+  const int spb = cube_spb<N, T>(p.tune.fft_spb > 0 ? p.tune.fft_spb : spread_slabs(batch, Cube<N>::LINES));
   const size_t lds = size_t(spb) * Cube<N>::SLAB * sizeof(cpx<T>);
   const int64_t blocks = (batch + spb - 1) / spb;
   const dim3 blk(spb * Cube<N>::LINES);

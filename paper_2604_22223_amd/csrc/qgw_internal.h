@@ -308,6 +308,18 @@ bool mf_grid_split(int n, int* n1, int* n2);
 hipError_t launch_row_map(const Plan& p, int64_t ncols, double sre, double sim, int herm, const void* in, void* out,
                           hipStream_t s);
 
+// Slabs per block of an untuned lattice transform (``lines`` threads each; the caller's limit still holds; 0: that limit):
+// as few as give one block to each of the 256 CUs, but at least a wavefront's lines.  FP64, against blocks filled to 256
+// threads: 64 slabs of 15 x 15 8.5 -> 6.1 us, 625 of 12 x 12 5.1 -> 4.5.  More than one block per CU lost again (two: 625
+// slabs of 36 x 36 12.0 -> 14.6 us, 900 of 30 x 30 11.2 -> 13.4), and so do small blocks where all lines fit into one,
+// whose other threads help to load and store (4 slabs of 20 x 20 4.6 -> 6.1 us).
+inline int spread_slabs(int64_t slabs, int lines) {
+  if (slabs * lines < 200) return 0;
+  const int64_t per_cu = (slabs + 255) / 256, wave = (64 + lines - 1) / lines;
+  const int64_t s = per_cu > wave ? per_cu : wave;
+  return s < 256 ? int(s) : 256;
+}
+
 // threads per slab line set: n for a square mesh, n^2 for a cube
 inline int lines_per_slab(const Plan& p) { return p.dim == 3 ? p.n * p.n : p.n; }
 // workspace: W^C (r N_k N_b^2 complex), then the Vbar partials (chunks N_k N_b^2)
