@@ -373,12 +373,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 // its strips on the matrix cores and writes whole 16-value runs of
 // the output.  Slab -> matrix: L = pair index a, W = q; matrix -> slab:
 // L = q, W = a.
-// A wave that has its operands goes first on its SIMD (s_setprio around the products), so the waves of a SIMD stay out
-// of step and the barriers of one block overlap the products of the other: five orbitals, 24 x 24, r = 53, a5 and a7
-// 226 and 211 -> 217 and 199 us in FP64, 150 and 128 -> 127 and 114 in FP32 (the same sums, bit for bit).  Two or
+// PRIO: a wave that has its operands goes first on its SIMD (s_setprio around the products), so that the waves of a SIMD
+// stay out of step and the barriers of one block overlap the products of the other.  Worth it from 512 columns per block
+// on; with one or two tiles a block it costs up to 7% (62,500 columns, r = 53, FP64: 52 -> 56 us).  Five orbitals,
+// 24 x 24, r = 53, a5 and a7: 227 and 211 us before both, 218 and 204 with the loads across tiles, 216 and 198 with the
+// priority as well; FP32 152 and 129, 129 and 117, 128 and 115 (the same sums, bit for bit).  Two or
 // four slices per barrier, one block of 16 waves per CU, and operands loaded straight into the matrix-core layout
 // with the output turned through LDS all measured slower (FP64 227-253 us for a5).
-template <typename T, int MT, int MODE, int WT>
+template <typename T, int MT, int MODE, int WT, bool PRIO>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_dlr_mfma_pairs(
     const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out, const cpx<T>* __restrict__ map, int r, int kp,
     int na, int nq, int tiles_l, int ntiles, T sre, T sim, int64_t in_ld) {
@@ -458,7 +460,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
         ar[mt] = tre[(kk * MT + mt) * 64 + lane];
         ai[mt] = tim[(kk * MT + mt) * 64 + lane];
       }
-      __builtin_amdgcn_s_setprio(1);
+      if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int w = 0; w < WT; ++w)
 #pragma unroll
@@ -473,7 +475,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
           accr[w][mt] = M::mac(-ai[mt], x[w].im, accr[w][mt]);
           acci[w][mt] = M::mac(ai[mt], x[w].re, acci[w][mt]);
         }
-      __builtin_amdgcn_s_setprio(0);
+      if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
     }
     const cpx<T> sc = mk(sre, sim);
 #pragma unroll
@@ -561,9 +563,11 @@ hipError_t dlr_mfma_pairs_launch(const Plan& p, int map, int na, int nq, double 
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   const cpx<T>* mp = map_ptr<T>(p, map);
-  // up to 96 columns per CU: at N_b = 2, 12 x 12 (576 columns) 20 -> 8 us; at N_b = 16, 9 x 9 (20,736) 25 -> 21-25 us in
-  // FP64, 24-26 -> 14-16 in FP32; at N_b = 9, 24 x 24 (46,656) it takes 51-56 us against 39-41
-  if (int64_t(na) * nq <= int64_t(96) * ncu) {
+  // few columns per CU (r = 53 unless said): at N_b = 2, 12 x 12 (576 columns) 20 -> 8 us.  FP32 up to 96: at N_b = 16,
+  // 9 x 9 (20,736) 24-26 -> 14-16 us.  In FP64 the row tiles read the input as often as there are: up to 60 (N_b = 4,
+  // 30 x 30, 14,400: 24 -> 20 us; N_b = 25, 6 x 6, 22,500: 24 -> 27), with one or two row tiles up to 44 (N_b = 5,
+  // 20 x 20, 10,000, r = 16: 4.5 -> 4.1 us; 24 x 24, 14,400: 4.6 -> 4.9)
+  if (int64_t(na) * nq <= int64_t(sizeof(T) == 4 ? 96 : mt <= 2 ? 44 : 60) * ncu) {
     const int tiles_i = (nW + 7) / 8, nts = tiles_i * ((nL + 1) / 2);
     const dim3 grid(unsigned((nts + 3) / 4), unsigned(mt));
 #define QGW_SMALL_SL(SLV)                                                                                      \
@@ -585,11 +589,17 @@ hipError_t dlr_mfma_pairs_launch(const Plan& p, int map, int na, int nq, double 
   int64_t blocks = ntiles;
   if (blocks > int64_t(bpc) * ncu) blocks = int64_t(bpc) * ncu;
   const size_t lds = size_t(2) * mt * 16 * kp * sizeof(T) + size_t(2) * 4 * 16 * (TW + 1) * sizeof(cpx<T>);
-#define QGW_MFMA_MT(MTV)                                                                                       \
-  case MTV:                                                                                                    \
-    hipLaunchKernelGGL((k_dlr_mfma_pairs<T, MTV, MODE, WT>), dim3(unsigned(blocks)), dim3(512), lds, s,        \
-                       (const cpx<T>*)in, (cpx<T>*)out, mp, p.r, kp, na, nq, tiles_l, ntiles, T(sre), T(sim), \
-                       in_ld);                                                                                 \
+  const bool prio = int64_t(ntiles) * 16 * TW >= 512 * blocks;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(unsigned(blocks)), dim3(512), lds, s, (const cpx<T>*)in, (cpx<T>*)out, mp, p.r, kp, na,
+                       nq, tiles_l, ntiles, T(sre), T(sim), in_ld);
+  };
+#define QGW_MFMA_MT(MTV)                              \
+  case MTV:                                           \
+    if (prio)                                         \
+      go(k_dlr_mfma_pairs<T, MTV, MODE, WT, true>);   \
+    else                                              \
+      go(k_dlr_mfma_pairs<T, MTV, MODE, WT, false>);  \
     break;
   switch (mt) {
     QGW_MFMA_MT(1)

@@ -45,3 +45,13 @@ def test_pair_maps_are_the_dense_product(rank, site_norb, n, precision):
         p.dlr_transform_pairs(which, qgw.LAYOUT_MATRIX, qgw.LAYOUT_SLAB, x.transpose(1, 2).contiguous(), z)
         assert bool(((z.to(torch.complex128) - ref).abs() <= bar).all())
     p.close()
+
+
+# on both sides of the lines between the kernels in FP64 (44 columns per CU of 256 with up to two row tiles, 60 with
+# more) and of the line for wave priority (512 columns per block of 512 blocks)
+@pytest.mark.parametrize("rank,site_norb,n", [(r, s, n) for r in (16, 32, 33, 64)
+                                              for s, n in (([2], 24), ([3], 12), ([2], 30), ([4], 8))]
+                         + [(33, [5], 18), (33, [5], 24)], ids=str)
+@pytest.mark.parametrize("precision", [qgw.F64, qgw.F32], ids=["f64", "f32"])
+def test_pair_maps_between_kernels(rank, site_norb, n, precision):
+    test_pair_maps_are_the_dense_product(rank, site_norb, n, precision)
