@@ -1560,6 +1560,9 @@ hipError_t dyson_w_t(const Plan& p, const void* v_q, const void* p_nu, void* wc_
     case 5: return dyson_w_small<5, T>(p, v_q, p_nu, wc_nu, s, ld);
     default: break;
   }
+  // the same at N_b = 9: FP64 212 matrices 6.0 against 8.4 us, 1,908 8.4 against 9.1, 2,400 9.9 against 9.5; FP32 640
+  // matrices 8.9 against 12.1, 2,560 10.6 against 13.1, 5,760 the same
+  if (p.nb == 9 && nmat < (sizeof(T) == 4 ? 6000 : 2200)) return dyson_wr<9, T>(p, v_q, p_nu, wc_nu, s, ld);
   // four matrices per wavefront; few larger ones (under six wavefronts of one matrix per SIMD) finish sooner one to a
   // wavefront: N_b = 16 with 1,908 matrices 10.6 against 18.4 us in FP32, with 7,632 the same
   if (p.nb >= 15 && nmat < 6000 && !guarded)

@@ -237,3 +237,35 @@ def test_copies_of_p_do_not_disturb_iterations():
         st.close()
     assert np.array_equal(sig[0], sig[1])
     p.close()
+
+
+@pytest.mark.parametrize("site_norb", [[3], [2, 2, 1], NINE_EIGHT], ids=str)
+@pytest.mark.parametrize("n,rank", [(1, 1), (3, 5), (6, 61), (6, 62)])
+@pytest.mark.parametrize("precision", [qgw.F64, qgw.F32], ids=["f64", "f32"])
+def test_dyson_w_of_few_nine_pair_matrices(site_norb, n, rank, precision):
+    """N_b = 9 on both sides of the 2,200 FP64 matrices from which a wavefront takes four, down to one matrix.  FP32: each
+    of the 9 elimination steps and the product V P leave an error of a few u relative to the entries; 4 N_b^2 u of the
+    largest entry holds at the condition these matrices have (below 4)."""
+    nk = n * n
+    rng = np.random.default_rng(rank)
+    nodes = dict(omega=np.linspace(-1.0, 1.0, rank), tau_t=np.linspace(0.1, 0.9, rank), n_f=np.arange(rank) - rank // 2,
+                 n_b=np.arange(rank) - rank // 2)
+    p = qgw.Plan.from_nodes(n, site_norb, 3.0, nodes, precision=precision)
+    nb = p.n_b
+    v = fold_v(rng, nk, site_norb) + 0.01 * rng.standard_normal((nk, nb, nb))
+    pnu = 0.02 * (rng.standard_normal((rank, nk, nb, nb)) + 1j * rng.standard_normal((rank, nk, nb, nb)))
+    c = torch.complex128 if precision == qgw.F64 else torch.complex64
+    vd, pd = dev(v).to(c), dev(pnu).to(c)
+    v, pnu = vd.cpu().numpy().astype(complex), pd.cpu().numpy().astype(complex)
+    a = np.eye(nb) - v[None] @ pnu
+    assert np.linalg.cond(a).max() < 4.0
+    out = torch.full_like(pd, float("nan"))
+    p.dyson_W(vd, pd, out)
+    p.sync_status()
+    ref = np.linalg.solve(a, np.broadcast_to(v[None], pnu.shape)) - v[None]
+    err = np.abs(out.cpu().numpy() - ref).max()
+    if precision == qgw.F64:
+        assert err < TOL * np.abs(ref).max()
+    else:
+        assert err < 4 * nb ** 2 * 2.0 ** -24 * np.abs(ref + v[None]).max()
+    p.close()
