@@ -868,7 +868,7 @@ static int64_t workspace_need(const Plan& p, int op) {
   switch (op) {
     case QGW_OP_SIGMA_BWD:
       return fo;  // Sigma-bar(k) -> R
-    case QGW_OP_DYSON_W_BWD:  // W^C per matrix, V-bar partials per chunk; r N_b^2 N_k more than used: the documented size
+    case QGW_OP_DYSON_W_BWD:  // W^C per matrix, V-bar partials per chunk (at most r)
       return (2 * int64_t(p.r) + (p.r < 8 ? p.r : 8)) * p.nb * p.nb * p.nk * int64_t(sizeof(zd));
     case QGW_OP_HARTREE_FOCK_BWD:
       return int64_t(p.nb) * p.nb * int64_t(sizeof(zd));  // V(q = 0)
@@ -986,7 +986,11 @@ qgw_status qgw_dyson_W_bwd(qgw_plan h, const void* V_q, const void* P_nu, const 
   QGW_REQUIRE(V_q && P_nu && Wcbar_nu && Pbar_nu && Vbar_q, QGW_ERR_INVALID_ARG, "qgw_dyson_W_bwd: null array");
   QGW_REQUIRE(Pbar_nu != P_nu && Pbar_nu != Wcbar_nu && Vbar_q != V_q, QGW_ERR_INVALID_ARG,
               "qgw_dyson_W_bwd: outputs alias inputs");
-  const int chunks = p.r < 8 ? p.r : 8;
+  // The nodes in eight chunks, from N_b = 16 on in more where few q leave the GPU idle: a block takes a q and a chunk,
+  // and r = 53 take 70 us in eight chunks of 4 q at N_b = 16, 29 in 53 (114 and 53 at N_b = 25).  With fewer pairs a
+  // chunk's work is short and the sum over the chunks longer than what they save (N_b = 1, 16 q: 11.5 us in eight, 18 in
+  // 53).  Each chunk's sums are one of the partials, which the workspace has room for at least r of.
+  const int chunks = std::min(p.r, p.nb >= 16 ? std::max(8, 1024 / p.nk) : 8);
   const int64_t nv = int64_t(p.nb) * p.nb * p.nk;
   QGW_WORKSPACE(QGW_OP_DYSON_W_BWD, workspace, workspace_bytes, "qgw_dyson_W_bwd");
   hipStream_t s = (hipStream_t)stream;

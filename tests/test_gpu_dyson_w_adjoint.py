@@ -57,3 +57,34 @@ def test_adjoint_of_every_size(nb):
     assert rel_err(pbar.cpu().numpy(), pb_ref) < 1e-10
     assert rel_err(vbar.cpu().numpy(), vb_ref) < 1e-10
     p.close()
+
+
+@pytest.mark.parametrize("n,rank", [(1, 1), (1, 70), (3, 40), (8, 15), (8, 17), (12, 9)])
+@pytest.mark.parametrize("nb", [1, 9, 16, 25])
+def test_adjoint_of_every_chunking(nb, n, rank):
+    """One q to more than the 128 from which the nodes go in eight chunks; chunks of one node and uneven ones (1, 70, 40,
+    15, 16 of 17, 8 of 9)."""
+    import torch
+    nodes = dict(omega=np.linspace(-1.0, 1.0, rank) if rank > 1 else np.array([0.5]), tau_t=(np.arange(rank) + 0.5) / rank,
+                 n_f=np.arange(rank) - rank // 2, n_b=np.arange(rank) - rank // 2)
+    p = qgw.Plan.from_nodes(n, SITES[nb], BETA, nodes)
+    rng = np.random.default_rng(100 * nb + rank)
+
+    def rand(*shape):
+        return rng.uniform(-1, 1, shape) + 1j * rng.uniform(-1, 1, shape)
+
+    vq, pnu, b = rand(p.n_k, nb, nb), rand(p.r, p.n_k, nb, nb) * (0.2 / nb), rand(p.r, p.n_k, nb, nb)
+    a = np.eye(nb) - vq[None] @ pnu
+    w = np.linalg.solve(a, np.broadcast_to(vq[None], pnu.shape))
+    x = np.linalg.solve(np.conj(np.swapaxes(a, -1, -2)), b)
+    wh, ph = np.conj(np.swapaxes(w, -1, -2)), np.conj(np.swapaxes(pnu, -1, -2))
+
+    def dev(y):
+        return torch.from_numpy(np.ascontiguousarray(y)).to("cuda:0")
+
+    pbar, vbar = dev(np.zeros_like(pnu)), dev(np.zeros_like(vq))
+    p.dyson_W_bwd(dev(vq), dev(pnu), dev(b), pbar, vbar)
+    p.sync_status()
+    assert rel_err(pbar.cpu().numpy(), wh @ b @ wh) < 1e-10
+    assert rel_err(vbar.cpu().numpy(), (x + x @ wh @ ph - b).sum(axis=0)) < 1e-10
+    p.close()
