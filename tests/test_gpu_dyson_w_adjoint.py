@@ -88,3 +88,44 @@ def test_adjoint_of_every_chunking(nb, n, rank):
     assert rel_err(pbar.cpu().numpy(), wh @ b @ wh) < 1e-10
     assert rel_err(vbar.cpu().numpy(), (x + x @ wh @ ph - b).sum(axis=0)) < 1e-10
     p.close()
+
+
+@pytest.mark.parametrize("sites", [[3], [2, 2, 1], [2, 1, 1, 1, 1, 1], [4], [2, 2, 2, 2], [3, 2, 1, 1, 1], [5], [4, 3]],
+                         ids=str)
+def test_adjoint_through_the_folded_solve(sites):
+    """5 x 32^2 matrices, past the 4,096 from which the forward solve of a V(q) with the pair-exchange symmetry goes through
+    the folded basis (all layouts that have one, and nine pairs in eight classes, which have not); every other q lacks the
+    symmetry and is left, marked in a workspace full of NaN, to the general kernel."""
+    import torch
+    n, rank = 32, 5
+    nodes = dict(omega=np.linspace(-1.0, 1.0, rank), tau_t=np.linspace(0.1, 0.9, rank), n_f=np.arange(rank) - 2,
+                 n_b=np.arange(rank) - 2)
+    p = qgw.Plan.from_nodes(n, sites, BETA, nodes)
+    nb, nk = p.n_b, p.n_k
+    rng = np.random.default_rng(nb + len(sites))
+
+    def rand(*shape):
+        return rng.uniform(-1, 1, shape) + 1j * rng.uniform(-1, 1, shape)
+
+    vq, pnu, b = rand(nk, nb, nb), rand(rank, nk, nb, nb) * (0.2 / nb), rand(rank, nk, nb, nb)
+    ex = _exchange(sites)
+    v = vq[::2] + vq[::2][:, ex]
+    vq[::2] = 0.25 * (v + v[:, :, ex])
+
+    def dev(y):
+        return torch.from_numpy(np.ascontiguousarray(y)).to("cuda:0")
+
+    pbar, vbar = dev(np.zeros_like(pnu)), dev(np.zeros_like(vq))
+    ws = p.workspace(1)  # QGW_OP_DYSON_W_BWD
+    ws.view(torch.float64).fill_(float("nan"))
+    p.dyson_W_bwd(dev(vq), dev(pnu), dev(b), pbar, vbar, workspace=ws)
+    p.sync_status()
+    some = np.unique(np.concatenate([[0, 1, 2, 3, nk - 2, nk - 1], rng.integers(0, nk, 20)]))
+    vs, ps, bs = vq[some][None], pnu[:, some], b[:, some]
+    a = np.eye(nb) - vs @ ps
+    w = np.linalg.solve(a, np.broadcast_to(vs, ps.shape))
+    x = np.linalg.solve(np.conj(np.swapaxes(a, -1, -2)), bs)
+    wh, ph = np.conj(np.swapaxes(w, -1, -2)), np.conj(np.swapaxes(ps, -1, -2))
+    assert rel_err(pbar.cpu().numpy()[:, some], wh @ bs @ wh) < 1e-10
+    assert rel_err(vbar.cpu().numpy()[some], (x + x @ wh @ ph - bs).sum(axis=0)) < 1e-10
+    p.close()

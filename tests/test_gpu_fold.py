@@ -269,3 +269,31 @@ def test_dyson_w_of_few_nine_pair_matrices(site_norb, n, rank, precision):
     else:
         assert err < 4 * nb ** 2 * 2.0 ** -24 * np.abs(ref + v[None]).max()
     p.close()
+
+
+@pytest.mark.parametrize("site_norb", [[2], [2, 1], [2, 2], [3], [2, 2, 1], NINE_EIGHT, [4], [2, 2, 2, 2], [3, 2, 1, 1, 1],
+                                       [5], [4, 3]], ids=str)
+@pytest.mark.parametrize("n", [3, 16])
+@pytest.mark.parametrize("symmetric", [True, False], ids=["folded", "full"])
+def test_single_precision_iteration_in_every_basis(site_norb, n, symmetric):
+    """One FP32 iteration from G0 in every number of classes, with few matrices and with more than the 6,000 from which all
+    sizes take four to a wavefront, against the FP64 iteration of the same state (held to the oracle above).  The bar is
+    that of the FP32 iteration elsewhere, 2e-4 of the largest entry: rounding 2^-24, amplified up to 56 times by the map
+    i nu -> tau, in sums of up to 64 nodes."""
+    w = wl.random_model((n, n), site_norb, seed=11, U=1.0, J=0.1, Vnn=0.1, beta=8.0, omega_max=16.0, eps=1e-9)
+    if not symmetric:
+        w["V_R"][(1, 1, 0, 0)] += 0.05
+    nodes = qgw.dlr_build(w["beta"] * w["omega_max"], w["eps"])
+    nodes["omega"] = nodes["x"] / w["beta"]
+    p = qgw.Plan.from_nodes(n, site_norb, w["beta"], nodes)
+    assert (p.r * p.n_k >= 6000) == (n == 16)
+    st = qgw.State(p, dev(flat(w["H_R"], 2)), dev(flat(w["V_R"], 2)), n_target=w["n_target"])
+    sig = []
+    for mode in (0, 2):
+        st.set_precision(mode)
+        st.init_g0()
+        st.iterate(1)
+        sig.append(st.array(1).cpu().numpy())
+    assert 0.0 < rel_err(sig[1], sig[0]) < 2e-4
+    st.close()
+    p.close()
