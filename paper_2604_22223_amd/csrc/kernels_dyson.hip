@@ -495,7 +495,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     int64_t ld, int* __restrict__ cond, int guarded = 0) {
   __shared__ cpx<T> xs[W25::XS];
   __shared__ cpx<T> sv[W25::NB * W25::NB];
-  if (guarded && !is_left_mark(wc[int64_t(blockIdx.x) * ld])) return;
+  if constexpr (sizeof(T) == 8) {
+    if (guarded && !is_left_mark(wc[int64_t(blockIdx.x) * ld])) return;
+  }
   w25_solve<T, MVP>(vq, pnu, wc, blockIdx.x, nk, ld, cond, xs, sv);
 }
 
@@ -1526,13 +1528,10 @@ hipError_t dyson_w_t(const Plan& p, const void* v_q, const void* p_nu, void* wc_
   if (ld < nn) return hipErrorInvalidValue;
   // FP32 calls on the caller's arrays keep the eliminations that follow, bit for bit: their rounding, amplified 19-56
   // times by the i nu -> tau map behind, shows at 1e-5 in W^C(tau), so another order of the same sums is another result
-  if (sizeof(T) == 4 && fold) {
-    switch (p.nb) {
-      case 8: return dyson_w_small<8, T>(p, v_q, p_nu, wc_nu, s, ld);
-      case 9: return dyson_wr<9, T>(p, v_q, p_nu, wc_nu, s, ld);
-      case 16: return dyson_wr<16, T>(p, v_q, p_nu, wc_nu, s, ld);
-      default: fold = false;
-    }
+  if constexpr (sizeof(T) == 4) {
+    if (fold && p.nb == 8) return dyson_w_small<8, T>(p, v_q, p_nu, wc_nu, s, ld);
+    if (fold && p.nb == 9) return dyson_wr<9, T>(p, v_q, p_nu, wc_nu, s, ld);
+    if (fold && p.nb == 16) return dyson_wr<16, T>(p, v_q, p_nu, wc_nu, s, ld);
   }
   // FP64, N_b >= 9: matrices whose V(q) has the pair-exchange symmetry are solved per unordered pair; the others are
   // left marked for the general kernel behind.  24 x 24, r = 53: 234 instead of 447 us (N_b = 25), 67 instead of 163
@@ -1545,7 +1544,7 @@ hipError_t dyson_w_t(const Plan& p, const void* v_q, const void* p_nu, void* wc_
     return a < b + nmat * ld * int64_t(sizeof(cpx<T>)) && b < a + count * int64_t(sizeof(cpx<T>));
   };
   bool guarded = false;
-  if (fold && !p.folded && fold_solver(p.nb, p.fold_nb) && nmat >= 4096 && !overlap(p_nu, nmat * nn) &&
+  if (sizeof(T) == 8 && fold && !p.folded && fold_solver(p.nb, p.fold_nb) && nmat >= 4096 && !overlap(p_nu, nmat * nn) &&
       !overlap(v_q, p.nk * nn)) {
     const hipError_t e = launch_dyson_wq_fold(p, v_q, p_nu, wc_nu, ld, s);
     if (e != hipSuccess) return e;

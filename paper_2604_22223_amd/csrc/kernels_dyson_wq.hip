@@ -158,7 +158,9 @@ __global__ __launch_bounds__(64) void k_dyson_wq(const cpx<T>* __restrict__ vq, 
   const int lane = threadIdx.x;
   const int q = int(blockIdx.x % unsigned(nk)), m0 = 4 * int(blockIdx.x / unsigned(nk));
   const int nv = min(4, r - m0);
-  if (guarded && !is_left_mark(wc[(int64_t(m0) * nk + q) * ld])) return;
+  if constexpr (sizeof(T) == 8) {
+    if (guarded && !is_left_mark(wc[(int64_t(m0) * nk + q) * ld])) return;
+  }
   for (int e = lane; e < NN; e += 64) su[e] = vq[int64_t(q) * NN + e];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -176,11 +178,12 @@ __global__ __launch_bounds__(64) void k_dyson_wq(const cpx<T>* __restrict__ vq, 
 
 // The same solve on full NF x NF pair matrices through the folded basis (NB classes): where V(q) is unchanged under
 // i <-> l of both indices, P is summed over the members of its classes as it is read and W^C written to every member;
-// elsewhere the group's matrices are marked and left to the general kernel.
-template <typename T, int NB, int NF>
-__global__ __launch_bounds__(64) void k_dyson_wq_fold(const cpx<T>* __restrict__ vq, const cpx<T>* __restrict__ pnu,
-                                                      cpx<T>* __restrict__ wc, int r, int nk, int64_t ld,
+// elsewhere the group's matrices are marked and left to the general kernel.  FP64 (FP32 calls keep their kernels).
+template <int NB, int NF>
+__global__ __launch_bounds__(64) void k_dyson_wq_fold(const zd* __restrict__ vq, const zd* __restrict__ pnu,
+                                                      zd* __restrict__ wc, int r, int nk, int64_t ld,
                                                       int* __restrict__ cond, const int* __restrict__ fold) {
+  using T = double;
   using S = WQ<NB>;
   constexpr int NN = S::NN, PS = S::PS, FF = NF * NF;
   __shared__ cpx<T> su[NN];
@@ -200,7 +203,7 @@ __global__ __launch_bounds__(64) void k_dyson_wq_fold(const cpx<T>* __restrict__
   if (!__any(bad))
     for (int e = lane + 64; e < FF; e += 64) bad |= differs(e);
   if (__any(bad)) {
-    if (lane < nv) wc[(int64_t(m0 + lane) * nk + q) * ld] = left_mark<T>();
+    if (lane < nv) wc[(int64_t(m0 + lane) * nk + q) * ld] = left_mark();
     return;
   }
   for (int e = lane; e < NN; e += 64) {
@@ -238,10 +241,10 @@ hipError_t wq_nb(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, 
   return hipGetLastError();
 }
 
-template <typename T, int NB, int NF>
+template <int NB, int NF>
 hipError_t wq_fold(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, int64_t ld, hipStream_t s) {
-  hipLaunchKernelGGL((k_dyson_wq_fold<T, NB, NF>), dim3(wq_blocks(p)), dim3(64), 0, s, (const cpx<T>*)v_q,
-                     (const cpx<T>*)p_nu, (cpx<T>*)wc_nu, p.r, p.nk, ld, p.d_status + kCondWord, p.d_fold_pairs);
+  hipLaunchKernelGGL((k_dyson_wq_fold<NB, NF>), dim3(wq_blocks(p)), dim3(64), 0, s, (const zd*)v_q, (const zd*)p_nu,
+                     (zd*)wc_nu, p.r, p.nk, ld, p.d_status + kCondWord, p.d_fold_pairs);
   return hipGetLastError();
 }
 
@@ -263,10 +266,9 @@ hipError_t launch_dyson_wq(const Plan& p, const void* v_q, const void* p_nu, voi
 
 hipError_t launch_dyson_wq_fold(const Plan& p, const void* v_q, const void* p_nu, void* wc_nu, int64_t ld,
                                 hipStream_t s) {
-#define QGW_CASE(NFV, NBV)                                                                     \
-  if (p.nb == NFV && p.fold_nb == NBV)                                                         \
-    return p.prec == 0 ? wq_fold<double, NBV, NFV>(p, v_q, p_nu, wc_nu, ld, s)                 \
-                       : wq_fold<float, NBV, NFV>(p, v_q, p_nu, wc_nu, ld, s);
+  if (p.prec != 0) return hipErrorInvalidValue;
+#define QGW_CASE(NFV, NBV) \
+  if (p.nb == NFV && p.fold_nb == NBV) return wq_fold<NBV, NFV>(p, v_q, p_nu, wc_nu, ld, s);
   QGW_FOR_EACH_FOLD(QGW_CASE)
 #undef QGW_CASE
   return hipErrorInvalidValue;

@@ -6,18 +6,11 @@ namespace qgw {
 
 // The mark that the folded Dyson-W kernel leaves in the first entry of a matrix it has not solved (a NaN pair that no
 // arithmetic makes).  A solved matrix that held it all the same would be solved once more by the general kernel.
-template <typename T>
-__device__ __forceinline__ cpx<T> left_mark() {
-  if constexpr (sizeof(T) == 8)
-    return mk(__longlong_as_double(0x7ff85157475f5701ll), __longlong_as_double(0x7ff85157475f5702ll));
-  else
-    return mk(__int_as_float(0x7fc51571), __int_as_float(0x7fc51572));
+__device__ __forceinline__ cpx<double> left_mark() {
+  return mk(__longlong_as_double(0x7ff85157475f5701ll), __longlong_as_double(0x7ff85157475f5702ll));
 }
 __device__ __forceinline__ bool is_left_mark(cpx<double> v) {
   return __double_as_longlong(v.re) == 0x7ff85157475f5701ll && __double_as_longlong(v.im) == 0x7ff85157475f5702ll;
-}
-__device__ __forceinline__ bool is_left_mark(cpx<float> v) {
-  return __float_as_int(v.re) == 0x7fc51571 && __float_as_int(v.im) == 0x7fc51572;
 }
 
 // row shift by DPP; a lane whose source lies outside its row gets INT_MIN, the identity of the max it feeds, so the
