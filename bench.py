@@ -113,7 +113,12 @@ PEAK_TFLOPS = {"f64": FP64_PEAK_TFLOPS, "f32": FP32_PEAK_TFLOPS}
 # profiles/hbm_traffic_gw_iteration_five_orbital_24.md).
 # Valid for the kernels as they were profiled; a changed kernel drops its entry until it is profiled again.
 MEASURED_TRAFFIC = {
-    "a14_delta_mix:f64": 37.8e6, "a14_delta_mix:f32": 37.8e6,
+    "a3a4_bubble:f64": 136.6e6, "a3a4_bubble:f32": 68.4e6,
+    "a5_dlr_p:f64": 234.1e6, "a5_dlr_p:f32": 121.2e6,
+    "a6_dyson_w:f64": 230.7e6, "a6_dyson_w:f32": 116.3e6,
+    "a7_dlr_w:f64": 229.8e6, "a7_dlr_w:f32": 113.8e6,
+    "a8a9a10_sigma:f64": 174.3e6, "a8a9a10_sigma:f32": 87.8e6,
+    "a14_delta_mix:f64": 37.9e6, "a14_delta_mix:f32": 37.9e6,
 }
 FP64_STEPS = ("a12_density_hf", "a14_delta_mix", "a13_dyson_g")
 
