@@ -1248,11 +1248,13 @@ __global__ __launch_bounds__(64) void k_dg_final(DysonGArgs A, int n, int nblk) 
 // six products and no system to solve: W comes from the forward solve, through the folded basis where V allows it.
 // (Solving A^H X = Wbar instead took two eliminations and a pass of X through memory.)  A small block per (q, chunk of
 // nodes), so that few waves wait for each other; a lane owns a tile of R x C entries of every product, and two products
-// that are ready together share a loop.  Each step loads R + C values from LDS for R C multiply-adds, and those loads
-// bound the kernel: at 25 x 25 the 2 x 3 tiles fill 117 lanes; 4 x 3 ones in a single wavefront load less, but LDS then
-// holds one wavefront per SIMD and its latency shows.  The FP64 matrix rate equals the vector rate, so padding 25 to 32
-// on the matrix cores would only add work.  The whole adjoint, 39 nodes, V without the symmetry, before and now:
-// N_b = 25 at 32 x 32 1960 -> 1700 us; at 24 x 24 N_b = 16 502 -> 411, 9 172 -> 95, 8 135 -> 71, 4 52 -> 32, 2 33 -> 20.
+// that are ready together share a loop.  Each step loads R + C values from LDS for R C multiply-adds.  At 48 x 48,
+// r = 59, N_b = 25 the vector unit issues 69% of the time, 93% of it multiply-adds, and a wavefront waits 27% of its time
+// (11% for LDS); LDS lets 1.9 wavefronts on a SIMD.  At 25 x 25 the 2 x 3 tiles fill 117 lanes; 4 x 3 ones in a single
+// wavefront load less, but LDS then holds one wavefront per SIMD and its latency shows.  The FP64 matrix rate equals the
+// vector rate, so padding 25 to 32 on the matrix cores would only add work.  The whole adjoint, 39 nodes, V without the
+// symmetry, before and now: N_b = 25 at 32 x 32 1960 -> 1700 us; at 24 x 24 N_b = 16 502 -> 411, 9 172 -> 95, 8 135 -> 71,
+// 4 52 -> 32, 2 33 -> 20.
 // V(q) is static, so Vbar(q) sums over the nodes: each block sums its chunk in a fixed order and writes a partial.
 // ---------------------------------------------------------------------------
 template <int NB>
@@ -1527,7 +1529,9 @@ hipError_t dyson_w_t(const Plan& p, const void* v_q, const void* p_nu, void* wc_
   if (ld == 0) ld = nn;
   if (ld < nn) return hipErrorInvalidValue;
   // FP32 calls on the caller's arrays keep the eliminations that follow, bit for bit: their rounding, amplified 19-56
-  // times by the i nu -> tau map behind, shows at 1e-5 in W^C(tau), so another order of the same sums is another result
+  // times by the i nu -> tau map behind, shows at 1e-5 in W^C(tau), and a caller's results stay what they were.  That
+  // is a choice and no limit: a state's FP32 phase solves its folded matrices in another order, and these sums in
+  // another lane layout would keep their bits
   if constexpr (sizeof(T) == 4) {
     if (fold && p.nb == 8) return dyson_w_small<8, T>(p, v_q, p_nu, wc_nu, s, ld);
     if (fold && p.nb == 9) return dyson_wr<9, T>(p, v_q, p_nu, wc_nu, s, ld);

@@ -71,7 +71,7 @@ __host__ __device__ __forceinline__ cpx<T> inv(cpx<T> a) {
   return mk(a.re * d, -a.im * d);
 }
 
-// a store that the caches need not keep, for an output larger than they are
+// a store that the caches need not keep (for which outputs that pays is its caller's rule)
 template <typename T>
 __device__ __forceinline__ void store_nt(cpx<T>* p, cpx<T> v) {
   __builtin_nontemporal_store(v.re, &p->re);
